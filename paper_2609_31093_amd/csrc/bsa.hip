@@ -10,19 +10,11 @@
 // are extracted by repeated wavefront arg-max (score desc, index asc).
 #include <algorithm>
 
+#include "bsa.h"
 #include "common.h"
 #include "kernels.h"
 
 namespace pisa {
-
-struct BsaArgs {
-  const void* q;
-  const float* pyr;
-  int32_t* idx;
-  int H, Hkv, G, Nq, N, C, K, causal, M1;
-  int64_t R;
-  float qscale2;
-};
 
 template <typename T, int D, int GMAX>
 __global__ __launch_bounds__(64) void bsa_rows_kernel(BsaArgs a) {
@@ -161,7 +153,10 @@ __global__ __launch_bounds__(64) void bsa_rows_kernel(BsaArgs a) {
 }
 
 // ----------------------------------------------------------------------------
-// MFMA flat selection (bf16 q).  One workgroup of four wavefronts per tile of
+// The exact list kernel (bf16 q): the tiles that the scan kernels of
+// bsa_scan.hip marked, and one head with 16 < K <= 32, which they do not take
+// (a lane sorts at most 32 collected blocks, and 64 classes put 45 above the
+// 32nd best of them).  One workgroup of four wavefronts per tile of
 // 64 consecutive query rows of one (batch, KV head).  The leaf means are
 // split once per call into bf16 hi + lo planes (bsa_hilo_kernel; hi + lo
 // reproduces the fp32 mean to ~2^-17 relative) and streamed through LDS in
@@ -251,8 +246,8 @@ __device__ __forceinline__ void bsa_cx(float& s, int& i, int lane, int j, bool a
 }
 
 template <int D, int KP, int GM>
-__global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint16_t* __restrict__ phi,
-                                                          const uint16_t* __restrict__ plo) {
+__device__ __forceinline__ void bsa_list_tile(const BsaArgs& a, const uint16_t* __restrict__ phi,
+                                              const uint16_t* __restrict__ plo, int tile, int bh) {
   constexpr int KS = D / 16;
   constexpr int LDS_ROW = D + 8;
   constexpr int CAP = 32;                      // blocks collected per query in the second scan
@@ -277,9 +272,8 @@ __global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint1
   const int col = lane & 31, half = lane >> 5;
   const int qh = wave & 1, bhalf = wave >> 1;
   const int q64 = qh * 32 + col, holder = bhalf * 2 + half;
-  const int bh = blockIdx.y;
   const int b = bh / a.Hkv, h = bh - b * a.Hkv;
-  const int row0 = blockIdx.x * 64;
+  const int row0 = tile * 64;
   const int rowc = min(row0 + q64, a.Nq - 1);
   const int c = (a.N - a.Nq + rowc) / a.C;
   const int elig = a.causal ? min(c + 1, a.M1) : a.M1;  // blocks [0, elig) are eligible
@@ -644,6 +638,40 @@ __global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint1
   }
 }
 
+// redo: only the tiles that the scan kernels marked; each workgroup looks at
+// 256 tiles' marks at a time.
+template <int D, int KP, int GM>
+__global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint16_t* __restrict__ phi,
+                                                          const uint16_t* __restrict__ plo, int BH, bool redo) {
+  const int ntx = (a.Nq + 63) / 64;
+  if (!redo) {
+    bsa_list_tile<D, KP, GM>(a, phi, plo, blockIdx.x % ntx, blockIdx.x / ntx);
+    return;
+  }
+  __shared__ int todo[256], ntodo;
+  const int64_t ntiles = static_cast<int64_t>(ntx) * BH;
+  const int64_t per = (ntiles + gridDim.x - 1) / gridDim.x;
+  const int64_t end = min(ntiles, per * (blockIdx.x + 1));
+  for (int64_t base = per * blockIdx.x; base < end; base += 256) {
+    __syncthreads();
+    if (threadIdx.x == 0) ntodo = 0;
+    __syncthreads();
+    const int64_t i = base + threadIdx.x;
+    if (i < end) {
+      const int64_t row = (i / ntx) * a.Nq + (i % ntx) * 64;
+      const bool more = (i % ntx) * 64 + 32 < a.Nq;
+      if (a.idx[row * a.K] == kBsaRedo || (more && a.idx[(row + 32) * a.K] == kBsaRedo))
+        todo[atomicAdd(&ntodo, 1)] = threadIdx.x;
+    }
+    __syncthreads();
+    for (int n = 0; n < ntodo; ++n) {
+      const int64_t t = base + todo[n];
+      bsa_list_tile<D, KP, GM>(a, phi, plo, static_cast<int>(t % ntx), static_cast<int>(t / ntx));
+      __syncthreads();
+    }
+  }
+}
+
 static bool bsa_mfma_path(const Shape& s) { return s.bf16 && s.K <= 32; }
 
 size_t bsa_ws(const Shape& s, const Geo& geo) {
@@ -680,8 +708,16 @@ hipError_t launch_flat_bsa(const Shape& s, const Geo& geo, const void* q, const 
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    const bool scan = bsa_scan_path(s.G, s.K);
+    if (scan) {
+      ProfScope ps("bsa_scan", st);
+      e = launch_bsa_scan(a, s.BH(), s.D, phi, plo, st);
+      if (e != hipSuccess) return e;
+    }
+    // After a scan: the marked tiles only, on a grid that a device holds.
     ProfScope ps("bsa_mfma", st);
-    dim3 grid((s.Nq + 63) / 64, s.BH());
+    const int64_t ntiles = static_cast<int64_t>((s.Nq + 63) / 64) * s.BH();
+    const unsigned grid = static_cast<unsigned>(scan ? std::min<int64_t>(ntiles, 512) : ntiles);
     const int KP = s.K <= 16 ? 16 : 32;
     // staged chunk (hi + lo rows), the score tile and the lists; the pass-1
     // merge reuses the chunk area
@@ -692,7 +728,7 @@ hipError_t launch_flat_bsa(const Shape& s, const Geo& geo, const void* q, const 
     auto go = [&](auto kern) {
       if (lds > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-      kern<<<grid, 256, lds, st>>>(a, phi, plo);
+      kern<<<grid, 256, lds, st>>>(a, phi, plo, s.BH(), scan);
     };
     auto by_g = [&](auto k1, auto k4, auto k16) {
       if (GM == 1) go(k1); else if (GM == 4) go(k4); else go(k16);
