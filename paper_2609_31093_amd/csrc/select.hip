@@ -25,10 +25,12 @@
 // hardware exp2/log2); the ranking is unchanged and exported scores are
 // converted back to natural log.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
 #include "sort32.h"
+#include "sortnet.h"
 
 namespace pisa {
 
@@ -1544,13 +1546,122 @@ __device__ __forceinline__ void g2_store_leaves(const SelArgs& a, int bh, int ro
 // D + 4 floats): the budget in floats.
 constexpr int kStageFloats = 16384;  // 64 KiB: two workgroups of 8 wavefronts per CU
 
-template <int D, int GMAX, int LPE, int KIND, int NWAVE, bool STAGE>
+// One candidate block's score for one row, by a whole wavefront: four lanes per
+// key, lane sub of them reading the 16-byte chunks sub, sub + 4, ... of the key
+// row, so that a load touches 16 rows' 64-byte runs (with a key per lane it
+// touched 64 rows, and the L1 delivered a quarter of its bytes: 84 us against
+// 38 at 2 x 4096 fp32 rows, d = 64; the 16-lane dots of select_kernel: 111).
+constexpr int kKeyLanes = 4;
+
+template <typename T, int D, int GMAX>
+__device__ __forceinline__ void key_query(const SelArgs& a, const T* __restrict__ q0, int sub,
+                                          float (&qk)[GMAX][D / kKeyLanes]) {
+  constexpr int E = 16 / sizeof(T);  // elements per 16-byte chunk
+#pragma unroll
+  for (int hh = 0; hh < GMAX; ++hh) {
+#pragma unroll
+    for (int i = 0; i < D / kKeyLanes; ++i) qk[hh][i] = 0.f;
+    if (hh < a.G) {
+#pragma unroll
+      for (int i = 0; i < D / kKeyLanes / E; ++i) {
+        float x[E];
+        load_row_part<T, E>(q0 + static_cast<int64_t>(hh) * a.Nq * D + (i * kKeyLanes + sub) * E, x);
+#pragma unroll
+        for (int e = 0; e < E; ++e) qk[hh][i * E + e] = x[e] * a.qscale2;
+      }
+    }
+  }
+}
+
+template <typename T, int D, int GMAX, int KIND>
+__device__ __forceinline__ float wave_block_score(const SelArgs& a, const T* __restrict__ kblk, int nrows,
+                                                  const float (&qk)[GMAX][D / kKeyLanes], int lane) {
+  constexpr int E = 16 / sizeof(T);
+  constexpr int KPP = 64 / kKeyLanes;  // keys per pass
+  const int sub = lane & (kKeyLanes - 1), key0 = lane / kKeyLanes;
+  // LSE: a running (max, sum) over passes of 64 keys; the other reducers: merged states
+  float m[GMAX], t[GMAX];
+  ScoreAcc st[GMAX];
+#pragma unroll
+  for (int hh = 0; hh < GMAX; ++hh) {
+    m[hh] = -INFINITY;
+    t[hh] = 0.f;
+    st[hh] = acc_empty(KIND);
+  }
+  for (int base = 0; base < nrows; base += 4 * KPP) {
+    float z[GMAX][4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int r = base + p * KPP + key0;
+      const T* kp = kblk + static_cast<int64_t>(min(r, nrows - 1)) * D + sub * E;
+      float acc[GMAX][2];
+#pragma unroll
+      for (int hh = 0; hh < GMAX; ++hh) acc[hh][0] = acc[hh][1] = 0.f;
+#pragma unroll
+      for (int i = 0; i < D / kKeyLanes / E; ++i) {
+        float x[E];
+        load_row_part<T, E>(kp + i * kKeyLanes * E, x);
+#pragma unroll
+        for (int hh = 0; hh < GMAX; ++hh) {  // heads past G have zero queries
+#pragma unroll
+          for (int e = 0; e < E; ++e) acc[hh][e & 1] = fmaf(x[e], qk[hh][i * E + e], acc[hh][e & 1]);
+        }
+      }
+#pragma unroll
+      for (int hh = 0; hh < GMAX; ++hh) {
+        float v = acc[hh][0] + acc[hh][1];
+        v += xor32_f<1>(v);
+        v += xor32_f<2>(v);
+        z[hh][p] = r < nrows ? v : -INFINITY;
+      }
+    }
+#pragma unroll
+    for (int hh = 0; hh < GMAX; ++hh) {
+      if constexpr (KIND == kScoreLse) {
+        const float mn = sel_max(sel_max(sel_max(z[hh][0], z[hh][1]), sel_max(z[hh][2], z[hh][3])), m[hh]);
+        const float ref = mn == -INFINITY ? 0.f : mn;
+        t[hh] *= fast_exp2(m[hh] - ref);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) t[hh] += fast_exp2(z[hh][p] - ref);
+        m[hh] = mn;
+      } else {
+        acc_merge(KIND, st[hh], acc_of<4>(KIND, z[hh]));
+      }
+    }
+  }
+  // over the 16 key groups (a key's four lanes hold the same)
+  float u = 0.f;
+#pragma unroll
+  for (int hh = 0; hh < GMAX; ++hh) {
+    if (hh < a.G) {
+      if constexpr (KIND == kScoreLse) {
+        auto at = [](float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); };
+        float mx = sel_max(dpp_f<0x128>(m[hh]), m[hh]);  // row_ror:8, row_ror:4
+        mx = sel_max(dpp_f<0x124>(mx), mx);
+        mx = sel_max(sel_max(at(mx, 0), at(mx, 16)), sel_max(at(mx, 32), at(mx, 48)));
+        float sm = t[hh] * fast_exp2(m[hh] - mx);
+        sm += dpp_f<0x128>(sm);
+        sm += dpp_f<0x124>(sm);
+        u += mx + fast_log2((at(sm, 0) + at(sm, 16)) + (at(sm, 32) + at(sm, 48)));
+      } else {
+#pragma unroll
+        for (int o = 32; o >= kKeyLanes; o >>= 1) acc_merge(KIND, st[hh], acc_shfl_xor(st[hh], o));
+        u += acc_value(KIND, st[hh]);
+      }
+    }
+  }
+  return u;
+}
+
+// FUSED: the walk goes on to the leaf level (raw keys, in T) and writes the
+// final selection; otherwise it stores the leaf candidates.
+template <typename T, int D, int GMAX, int LPE, int KIND, int NWAVE, bool STAGE, bool FUSED = false>
 __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
   constexpr int DPL = D / LPE;
   constexpr int NCH = DPL / 4;
   constexpr int SROW = D + 4;
   const Geo& geo = a.geo;
-  const int G = a.G, K = a.K, gK = a.gK;
+  const int G = a.G, K = a.K;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, hl = lane & 31, hbase = lane & 32;
   const int sub = hl % LPE;
@@ -1564,7 +1675,7 @@ __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
 
   float qv[GMAX][DPL];
   {
-    const uint16_t* qb = static_cast<const uint16_t*>(a.q);
+    const T* qb = static_cast<const T*>(a.q);
 #pragma unroll
     for (int hh = 0; hh < GMAX; ++hh) {
       if (hh < G) {
@@ -1572,7 +1683,7 @@ __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
           float x4[4];
-          load_row_part<uint16_t, 4>(qb + off + ch * 4 * LPE, x4);
+          load_row_part<T, 4>(qb + off + ch * 4 * LPE, x4);
 #pragma unroll
           for (int e = 0; e < 4; ++e) qv[hh][ch * 4 + e] = x4[e] * a.qscale2;
         }
@@ -1673,7 +1784,64 @@ __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
     g2_rank_expand<GMAX, KIND>(geo, lev, c, a.causal, K, G, start, hl, hbase, node, z0, z1, zs);
   }
   if (start == 1) node = hl < n_eligible(1) ? hl : -1;  // every eligible leaf, unranked
-  g2_store_leaves(a, bh, row, live, hl, hbase, node);
+  if constexpr (!FUSED) {
+    g2_store_leaves(a, bh, row, live, hl, hbase, node);
+  } else {
+    // Leaf candidates in ascending order, lane hl of a half.
+    const int nA = __builtin_popcount(static_cast<uint32_t>(__ballot(node >= 0) >> hbase));
+    float akey = node >= 0 ? -static_cast<float>(node) : -INFINITY;
+    int apack = node >= 0 ? node : 0x7FFFFFC0 | hl;
+    sort32(akey, apack, hl);
+    const bool valid = hl < nA;
+    const int leaf = valid ? apack : -1;
+    const bool isf = a.causal && valid && (leaf == 0 || leaf == c || leaf == c - 1);
+    const bool ranked = nA > K;
+    // Both rows' scored candidates, one after another on the whole wavefront.
+    float us = 0.f;
+    const uint64_t todo = __ballot(valid && ranked && !isf && live);
+    const T* kbh = static_cast<const T*>(a.k) + static_cast<int64_t>(bh) * geo.Nkv * D;
+#pragma unroll
+    for (int hb = 0; hb < 2; ++hb) {
+      uint32_t mine = static_cast<uint32_t>(todo >> (32 * hb));
+      if (mine == 0) continue;
+      const int rw = __builtin_amdgcn_readlane(row, 32 * hb);
+      float qk[GMAX][D / kKeyLanes];
+      key_query<T, D, GMAX>(a, static_cast<const T*>(a.q) + ((static_cast<int64_t>(b) * a.H + h * G) * a.Nq + rw) * D,
+                            lane & (kKeyLanes - 1), qk);
+      while (mine) {
+        const int l = 32 * hb + __ffs(mine) - 1;
+        mine &= mine - 1;
+        const int r0 = __builtin_amdgcn_readlane(leaf, l) * geo.C;
+        const float u = wave_block_score<T, D, GMAX, KIND>(a, kbh + static_cast<int64_t>(r0) * D,
+                                                           min(geo.C, geo.N - r0), qk, lane);
+        us = lane == l ? u : us;
+      }
+    }
+    // The first K in (score desc, block asc) order, forced blocks first, back
+    // in ascending order.
+    __shared__ int s_rank[NWAVE][64];
+    float key = -INFINITY;
+    if (valid) key = ranked && !isf ? us : INFINITY;
+    const float own = key;
+    int pack = valid ? (leaf << 6) | hl : 0x7FFFFFC0 | hl;
+    sort32(key, pack, hl);
+    s_rank[wave][hbase + (pack & 63)] = hl;
+    wave_sync();
+    const bool kept = valid && s_rank[wave][lane] < K;
+    const int incl = scan32(kept ? 1 : 0, hl);
+    const int total = half_total(incl, lane);
+    if (live) {
+      const int64_t orow = (static_cast<int64_t>(bh) * a.Nq + row) * K;
+      if (kept) {
+        a.idx[orow + incl - 1] = leaf;
+        if (a.score) a.score[orow + incl - 1] = own == INFINITY ? INFINITY : own * kLn2;
+      }
+      if (hl >= total && hl < K) {
+        a.idx[orow + hl] = -1;
+        if (a.score) a.score[orow + hl] = -INFINITY;
+      }
+    }
+  }
 }
 
 // Final Top-K for g*K <= 32: a row per 32-lane half of a wavefront (RP such
@@ -2440,6 +2608,37 @@ hipError_t launch_select_fused(const Shape& s, const Geo& geo, const void* q, co
   // Few rows: a whole workgroup per row to cut latency; many rows: a wave per row.
   const bool wide = static_cast<int64_t>(s.BH()) * s.Nq <= 2048;
   ProfScope ps("select_fused", st);
+  if (!wide && s.g == 2 && s.gK() <= 32 && s.G <= 4) {
+    dim3 grid((s.Nq + 7) / 8, s.BH());
+    auto go = [&](auto k0, auto k1, auto k2) {
+      if (s.score == kScoreLse) k0<<<grid, 256, 0, st>>>(a);
+      else if (s.score == kScoreMean) k1<<<grid, 256, 0, st>>>(a);
+      else k2<<<grid, 256, 0, st>>>(a);
+    };
+    auto by_shape = [&](auto t) {
+      using T = decltype(t);
+      auto kinds = [&](auto d, auto gm, auto lpe) {
+        constexpr int D = decltype(d)::value, GM = decltype(gm)::value, LPE = decltype(lpe)::value;
+        go(stage1_g2_kernel<T, D, GM, LPE, kScoreLse, 4, false, true>,
+           stage1_g2_kernel<T, D, GM, LPE, kScoreMean, 4, false, true>,
+           stage1_g2_kernel<T, D, GM, LPE, kScoreMeanVar, 4, false, true>);
+      };
+      using std::integral_constant;
+      if (s.D == 128 && s.G == 1)
+        kinds(integral_constant<int, 128>{}, integral_constant<int, 1>{}, integral_constant<int, 16>{});
+      else if (s.D == 128)
+        kinds(integral_constant<int, 128>{}, integral_constant<int, 4>{}, integral_constant<int, 8>{});
+      else if (s.G == 1)
+        kinds(integral_constant<int, 64>{}, integral_constant<int, 1>{}, integral_constant<int, 16>{});
+      else
+        kinds(integral_constant<int, 64>{}, integral_constant<int, 4>{}, integral_constant<int, 8>{});
+    };
+    if (s.bf16)
+      by_shape(uint16_t{});
+    else
+      by_shape(float{});
+    return hipGetLastError();
+  }
   if (s.bf16) {
     if (wide)
       launch_sel_d<uint16_t, 256, true>(s, a, st);
@@ -2551,18 +2750,18 @@ static hipError_t launch_two_stage_heads(const Shape& s, const Geo& geo, const v
       if (s.g == 2 && s.G <= 4) {
         if (s.D == 128) {
           if (s.G == 1)
-            by_kind(stage1_g2_kernel<128, 1, 16, kScoreLse, 8, true>, stage1_g2_kernel<128, 1, 16, kScoreMean, 8, true>,
-                    stage1_g2_kernel<128, 1, 16, kScoreMeanVar, 8, true>);
+            by_kind(stage1_g2_kernel<uint16_t, 128, 1, 16, kScoreLse, 8, true>, stage1_g2_kernel<uint16_t, 128, 1, 16, kScoreMean, 8, true>,
+                    stage1_g2_kernel<uint16_t, 128, 1, 16, kScoreMeanVar, 8, true>);
           else
-            by_kind4(stage1_g2_kernel<128, 4, 8, kScoreLse, 4, false>, stage1_g2_kernel<128, 4, 8, kScoreMean, 4, false>,
-                     stage1_g2_kernel<128, 4, 8, kScoreMeanVar, 4, false>);
+            by_kind4(stage1_g2_kernel<uint16_t, 128, 4, 8, kScoreLse, 4, false>, stage1_g2_kernel<uint16_t, 128, 4, 8, kScoreMean, 4, false>,
+                     stage1_g2_kernel<uint16_t, 128, 4, 8, kScoreMeanVar, 4, false>);
         } else {
           if (s.G == 1)
-            by_kind(stage1_g2_kernel<64, 1, 16, kScoreLse, 8, true>, stage1_g2_kernel<64, 1, 16, kScoreMean, 8, true>,
-                    stage1_g2_kernel<64, 1, 16, kScoreMeanVar, 8, true>);
+            by_kind(stage1_g2_kernel<uint16_t, 64, 1, 16, kScoreLse, 8, true>, stage1_g2_kernel<uint16_t, 64, 1, 16, kScoreMean, 8, true>,
+                    stage1_g2_kernel<uint16_t, 64, 1, 16, kScoreMeanVar, 8, true>);
           else
-            by_kind4(stage1_g2_kernel<64, 4, 8, kScoreLse, 4, false>, stage1_g2_kernel<64, 4, 8, kScoreMean, 4, false>,
-                     stage1_g2_kernel<64, 4, 8, kScoreMeanVar, 4, false>);
+            by_kind4(stage1_g2_kernel<uint16_t, 64, 4, 8, kScoreLse, 4, false>, stage1_g2_kernel<uint16_t, 64, 4, 8, kScoreMean, 4, false>,
+                     stage1_g2_kernel<uint16_t, 64, 4, 8, kScoreMeanVar, 4, false>);
         }
       } else if (s.D == 128) {
         if (s.G == 1) go(stage1_pair_kernel<128, 1, 4>);
