@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "attn_shared.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -185,26 +186,6 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
 // attn_combine_kernel merges the partials of each (row, head) with the usual
 // log-sum-exp weights.
 // ----------------------------------------------------------------------------
-
-typedef __bf16 bf16x8a __attribute__((ext_vector_type(8)));
-typedef float f32x4a __attribute__((ext_vector_type(4)));
-
-struct AttnBlockArgs {
-  int H, Hkv, G, Nq, N, C, K, causal, M1;
-  int row0, nrows;  // row chunk handled by this launch
-  float qscale2;
-  int Nkv;          // rows per (batch, KV head) in k and v
-  // rows attended by the row-tile union kernel (flag per tile of
-  // 1 << skip_shift rows); the block-centric kernels leave them alone
-  const uint8_t* skip = nullptr;
-  int skip_shift = 0, skip_tiles = 0;
-};
-
-__device__ __forceinline__ bool union_row(const AttnBlockArgs& a, int bh, int row) {
-  return a.skip && a.skip[static_cast<int64_t>(bh) * a.skip_tiles + (row >> a.skip_shift)];
-}
-
-__device__ __forceinline__ bf16x8a u4_as_bf16x8(uint4 r) { return __builtin_bit_cast(bf16x8a, r); }
 
 constexpr int kAttnChunk = 1024;  // pairs of one selected-block cluster per workgroup (key block staged once)
 constexpr int kAttnBlockWaves = 8;  // wavefronts per workgroup of attn_block16_kernel
@@ -415,7 +396,7 @@ __global__ __launch_bounds__(NW * 64, (CT >= 3 ? 1 : NW == 8 ? 4 : 3)) void attn
         uint2 w;
         w.x = pack2_bf16(oacc[dt][0] * inv, oacc[dt][1] * inv);
         w.y = pack2_bf16(oacc[dt][2] * inv, oacc[dt][3] * inv);
-        *reinterpret_cast<uint2*>(tb + col * TBS + dt * 16 + 4 * grp) = w;
+        *reinterpret_cast<uint2*>(tb + col * TBS + (a.tile_order ? (dt >> 1) * 32 + grp * 8 + (dt & 1) * 4 : dt * 16 + 4 * grp)) = w;
       }
       if (valid && grp == 0) part_lse[pidx] = l > 0.f ? m + fast_log2(l) : -INFINITY;
       wave_sync();
@@ -825,32 +806,8 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnBlockArgs a, cons
 // block-centric kernels skip the rows of flagged tiles.
 // ----------------------------------------------------------------------------
 constexpr int kUnionWaves = 8;
-constexpr int kUnionGroups = 2;   // 16-column groups per wavefront
 constexpr int kUnionCols = kUnionWaves * kUnionGroups * 16;
 constexpr int kUnionMaxU = 256;   // union limit: at most min(3K, 256) blocks
-constexpr float kUnionSlack = 8.f;  // log2 units the running maximum may lag behind
-constexpr size_t kUnionMaxLds = 160 * 1024;  // LDS of one CU
-constexpr int kUnionMergeBatch = 4;  // LOCAL: partials requested together
-constexpr int kLocalWaves = 4;       // LOCAL: wavefronts per workgroup (several workgroups per CU)
-constexpr int kDeviceCUs = 256;
-// LDS byte address of a pointer into dynamic shared memory, made wave-uniform.
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const char*)p)));
-}
-// 16 bytes per lane from global memory straight into LDS at lds + 16 * lane.
-// Issued from inline assembly so that the compiler does not make the next
-// LDS read wait for it (it cannot tell the two stages apart); the consumer
-// waits for it with an explicit vmcnt wait and a barrier.
-__device__ __forceinline__ void lds_dma16(const void* src, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds) : "memory", "m0");
-}
-// Chunk-position swizzle of a staged key row (NCH 16-byte chunks per row):
-// the 16 rows of a K operand read get 16 distinct bank positions.
-template <int NCH>
-__device__ __forceinline__ int union_swz(int r) {
-  return NCH == 16 ? (r & 15) : ((r >> 1) & 7);
-}
 // Fewest flagged tiles the union kernel takes: four per CU of the 256-CU
 // device, so that its persistent grid (two workgroups per CU) runs at least
 // two rounds of tiles.
@@ -963,19 +920,12 @@ __global__ __launch_bounds__(1024) void attn_union_compact_kernel(uint8_t* __res
   if (tid == 0) *count = base;
 }
 
-// LOCAL (causal, block-centric path): the tiles of the chunk [a.row0,
-// a.row0 + a.nrows) that the union kernel did not take, each over the union
-// of its rows' first, previous and own blocks only (the ones they selected);
-// every column then merges the partials the block-centric kernel wrote for
-// its row's other slots before o and lse are written.  ltiles: tiles per
-// (batch, KV head) in the chunk, lcount: ltiles times the groups.
-template <int D, int CT, int G, bool LOCAL>
-__global__ __launch_bounds__((LOCAL ? kLocalWaves : kUnionWaves) * 64, 2) void attn_union_kernel(
+template <int D, int CT, int G>
+__global__ __launch_bounds__(kUnionWaves * 64, 2) void attn_union_kernel(
     AttnBlockArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ idx, uint16_t* __restrict__ o, float* __restrict__ lse,
-    const int32_t* __restrict__ tile_list, const int32_t* __restrict__ tile_count,
-    const uint16_t* __restrict__ part_o, const float* __restrict__ part_lse, int ltiles, int lcount) {
-  constexpr int NW = LOCAL ? kLocalWaves : kUnionWaves, NG = kUnionGroups;
+    const int32_t* __restrict__ tile_list, const int32_t* __restrict__ tile_count) {
+  constexpr int NW = kUnionWaves, NG = kUnionGroups;
   constexpr int RW = 16 * NG / G, T = NW * RW;  // rows per wavefront, per tile
   constexpr int KS = D / 32;
   constexpr int C = CT * 32;
@@ -1002,33 +952,15 @@ __global__ __launch_bounds__((LOCAL ? kLocalWaves : kUnionWaves) * 64, 2) void a
   __shared__ int s_nu;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ntile = LOCAL ? lcount : *tile_count;
-  const int rend = LOCAL ? min(a.Nq, a.row0 + a.nrows) : a.Nq;  // rows of this launch end here
+  const int ntile = *tile_count;
   // persistent workgroups over the tiles
   for (int li = blockIdx.x; li < ntile; li += gridDim.x) {
-  int bh, tile;
-  if constexpr (LOCAL) {
-    bh = li / ltiles;
-    tile = a.row0 / T + (li - bh * ltiles);
-    // the union kernel's tiles (T divides its tile rows)
-    if (a.skip && a.skip[static_cast<int64_t>(bh) * a.skip_tiles + ((tile * T) >> a.skip_shift)]) continue;
-  } else {
-    const int id = tile_list[li];
-    bh = id / a.skip_tiles;
-    tile = id - bh * a.skip_tiles;
-  }
+  const int id = tile_list[li];
+  const int bh = id / a.skip_tiles, tile = id - bh * a.skip_tiles;
   const int b = bh / a.Hkv, h = bh - b * a.Hkv;
   const int r0 = tile * T;
   const int32_t* lst = idx + static_cast<int64_t>(bh) * a.Nq * a.K;
-  // LOCAL: only a row's first, previous and own blocks (App. B's forced set)
-  auto take = [&](int row, int x) {
-    if (x < 0 || x >= a.M1) return false;
-    if constexpr (LOCAL) {
-      const int cr = (a.N - a.Nq + row) / C;
-      return x == 0 || x == cr || x == cr - 1;
-    }
-    return true;
-  };
+  auto take = [&](int x) { return x >= 0 && x < a.M1; };
 
   __syncthreads();  // the previous tile's readers of the LDS are done
   for (int e = tid; e < MW; e += NW * 64) bitmap[e] = 0;
@@ -1036,9 +968,9 @@ __global__ __launch_bounds__((LOCAL ? kLocalWaves : kUnionWaves) * 64, 2) void a
   __syncthreads();
   for (int e = tid; e < T * a.K; e += NW * 64) {
     const int row = r0 + e / a.K;
-    if (row >= rend) continue;
+    if (row >= a.Nq) continue;
     const int x = lst[static_cast<int64_t>(row) * a.K + e % a.K];
-    if (take(row, x)) atomicOr(&bitmap[x >> 5], 1u << (x & 31));
+    if (take(x)) atomicOr(&bitmap[x >> 5], 1u << (x & 31));
   }
   __syncthreads();
   if (wave == 0) {
@@ -1071,9 +1003,9 @@ __global__ __launch_bounds__((LOCAL ? kLocalWaves : kUnionWaves) * 64, 2) void a
   }
   for (int e = tid; e < T * a.K; e += NW * 64) {
     const int j = e / a.K, row = r0 + j;
-    if (row >= rend) continue;
+    if (row >= a.Nq) continue;
     const int x = lst[static_cast<int64_t>(row) * a.K + e % a.K];
-    if (!take(row, x)) continue;
+    if (!take(x)) continue;
     const int u = wpre[x >> 5] + __builtin_popcount(bitmap[x >> 5] & ((1u << (x & 31)) - 1u));
     if (u < kUnionMaxU) atomicOr(&rmask[j * MWU + (u >> 5)], 1u << (u & 31));
   }
@@ -1091,7 +1023,7 @@ __global__ __launch_bounds__((LOCAL ? kLocalWaves : kUnionWaves) * 64, 2) void a
     const int cc = cg * 16 + col;
     jr[cg] = wave * RW + cc / G;
     const int row = r0 + jr[cg];
-    vrow[cg] = row < rend;
+    vrow[cg] = row < a.Nq;
     const int rowc = vrow[cg] ? row : r0;
     tq[cg] = a.N - a.Nq + rowc;
     const uint16_t* qrow = q + ((static_cast<int64_t>(b) * a.H + h * G + cc % G) * a.Nq + rowc) * D + grp * 8;
@@ -1270,86 +1202,8 @@ __global__ __launch_bounds__((LOCAL ? kLocalWaves : kUnionWaves) * 64, 2) void a
     float ll = l[cg];
     ll += __shfl_xor(ll, 16);
     ll += __shfl_xor(ll, 32);
-    float mm = m[cg];
+    const float mm = m[cg];
     const int cc = cg * 16 + col;
-    if constexpr (LOCAL) {
-      // merge the partials (o normalised, log2-sum) of the row's other
-      // slots.  The four lanes of a column request the slot indices, then
-      // the log-sums, of slots grp, grp + 4, ... (the first 32) all at once;
-      // the partials (each lane the 4 values of each 16-wide d tile it
-      // holds) follow in batches of four slots.
-      const int row = tq[cg] - (a.N - a.Nq);
-      const int cr = tq[cg] / C;
-      const int hq = cc % G;
-      const int32_t* sl = lst + static_cast<int64_t>(row) * a.K;
-      const int64_t pb = (static_cast<int64_t>(bh) * a.nrows + (row - a.row0)) * a.K;
-      auto far = [&](int x) { return x >= 0 && x < a.M1 && x != 0 && x != cr && x != cr - 1; };
-      constexpr int KB = 8;  // the first 4 * KB slots: KB per lane
-      int xs[KB];
-      float lsv[KB];
-#pragma unroll
-      for (int i = 0; i < KB; ++i) xs[i] = 4 * i + grp < a.K ? sl[4 * i + grp] : -1;
-#pragma unroll
-      for (int i = 0; i < KB; ++i) lsv[i] = far(xs[i]) ? part_lse[(pb + 4 * i + grp) * G + hq] : -INFINITY;
-      const uint16_t* pcol = part_o + (pb * G + hq) * D + 4 * grp;  // slot s at pcol + s * G * D
-      auto merge = [&](const float (&ls)[kUnionMergeBatch], const uint2 (&xo)[kUnionMergeBatch][DT])
-                       __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < kUnionMergeBatch; ++u) {
-          if (ls[u] == -INFINITY) continue;
-          const float mn = fmaxf(mm, ls[u]);
-          const float c0 = fast_exp2(mm - mn), c1 = fast_exp2(ls[u] - mn);
-          ll = ll * c0 + c1;
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            oacc[cg][dt][0] = oacc[cg][dt][0] * c0 + __uint_as_float(xo[u][dt].x << 16) * c1;
-            oacc[cg][dt][1] = oacc[cg][dt][1] * c0 + __uint_as_float(xo[u][dt].x & 0xFFFF0000u) * c1;
-            oacc[cg][dt][2] = oacc[cg][dt][2] * c0 + __uint_as_float(xo[u][dt].y << 16) * c1;
-            oacc[cg][dt][3] = oacc[cg][dt][3] * c0 + __uint_as_float(xo[u][dt].y & 0xFFFF0000u) * c1;
-          }
-          mm = mn;
-        }
-      };
-      static_assert(kUnionMergeBatch == 4, "a batch is the four slots of one register of lsv");
-      // batch i = slots 4 i .. 4 i + 3; slot 4 i + u is held by lane col + 16 u
-      auto fetch = [&](int i, float (&ls)[kUnionMergeBatch], uint2 (&xo)[kUnionMergeBatch][DT])
-                       __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < kUnionMergeBatch; ++u) {
-          ls[u] = __shfl(lsv[i], col | (u << 4));
-          const uint16_t* pr = pcol + static_cast<int64_t>(ls[u] != -INFINITY ? 4 * i + u : 0) * G * D;
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) xo[u][dt] = *reinterpret_cast<const uint2*>(pr + dt * 16);
-        }
-      };
-      const int nb = min(a.K, 4 * KB);
-#pragma unroll
-      for (int i = 0; i < KB; ++i) {
-        if (4 * i >= nb) break;
-        float ls[kUnionMergeBatch];
-        uint2 xo[kUnionMergeBatch][DT];
-        fetch(i, ls, xo);
-        merge(ls, xo);
-      }
-      // slots 32 and up (budgets above 32), a batch at a time
-      for (int s0 = 4 * KB; s0 < a.K; s0 += kUnionMergeBatch) {
-        float ls[kUnionMergeBatch];
-        uint2 xo[kUnionMergeBatch][DT];
-#pragma unroll
-        for (int u = 0; u < kUnionMergeBatch; ++u) {
-          const int sx = s0 + u;
-          const int x = sx < a.K ? sl[sx] : -1;
-          ls[u] = far(x) ? part_lse[(pb + sx) * G + hq] : -INFINITY;
-        }
-#pragma unroll
-        for (int u = 0; u < kUnionMergeBatch; ++u) {
-          const uint16_t* pr = pcol + static_cast<int64_t>(ls[u] != -INFINITY ? s0 + u : 0) * G * D;
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) xo[u][dt] = *reinterpret_cast<const uint2*>(pr + dt * 16);
-        }
-        merge(ls, xo);
-      }
-    }
     if (!vrow[cg]) continue;
     // oacc[cg][dt][i] = O[d = dt*16 + 4*grp + i][this column]
     const int64_t orow = (static_cast<int64_t>(b) * a.H + h * G + cc % G) * a.Nq + r0 + jr[cg];
@@ -1669,7 +1523,7 @@ static hipError_t launch_block_path(const Shape& s, const Geo& geo, const void* 
       const unsigned ugrid = static_cast<unsigned>(std::min(s.BH() * skip_tiles, per_cu * kDeviceCUs));
       kern<<<ugrid, kUnionWaves * 64, ulds, st>>>(ua, static_cast<const uint16_t*>(q),
                                                   static_cast<const uint16_t*>(k), static_cast<const uint16_t*>(v), idx,
-                                                  static_cast<uint16_t*>(o), lse, tlist, tcount, nullptr, nullptr, 0, 0);
+                                                  static_cast<uint16_t*>(o), lse, tlist, tcount);
     };
     auto by_g = [&](auto k1, auto k2, auto k4, auto k8, auto k16) {
       switch (s.G) {
@@ -1681,8 +1535,8 @@ static hipError_t launch_block_path(const Shape& s, const Geo& geo, const void* 
       }
     };
 #define PISA_UNION(CT) \
-    by_g(attn_union_kernel<D, CT, 1, false>, attn_union_kernel<D, CT, 2, false>, attn_union_kernel<D, CT, 4, false>, \
-         attn_union_kernel<D, CT, 8, false>, attn_union_kernel<D, CT, 16, false>)
+    by_g(attn_union_kernel<D, CT, 1>, attn_union_kernel<D, CT, 2>, attn_union_kernel<D, CT, 4>, \
+         attn_union_kernel<D, CT, 8>, attn_union_kernel<D, CT, 16>)
     if (s.C == 32) PISA_UNION(1);
     else if (s.C == 64) PISA_UNION(2);
     else if (s.C == 96) PISA_UNION(3);
@@ -1701,6 +1555,7 @@ static hipError_t launch_block_path(const Shape& s, const Geo& geo, const void* 
     if ((e = launch_cluster(ca, s.BH(), base + w.cl, &co, st, kAttnChunk)) != hipSuccess) return e;
     AttnBlockArgs a{s.H, s.Hkv, s.G, s.Nq, s.N, s.C, s.K, s.causal, geo.M[1], row0, nrows,
                     kLog2e / sqrtf(static_cast<float>(s.D)), s.Nkv, skip, skip_shift, skip_tiles};
+    a.tile_order = local && s.G > 1 && union_ok(s) && row0 % attn_tile_rows(s.G) == 0;
     {
       ProfScope ps("attn_block", st);
       dim3 grid(static_cast<unsigned>(
@@ -1727,45 +1582,15 @@ static hipError_t launch_block_path(const Shape& s, const Geo& geo, const void* 
         go(attn_block16_kernel<D, 4, kAttnBlockWaves>, kAttnBlockWaves);
     }
     // With several heads per KV head, the row tiles of this chunk that the
-    // union kernel did not take go through its LOCAL mode: the forced blocks
-    // staged once per tile for every head, then the far partials merged.
-    const int lT = union_ok(s) ? kLocalWaves * kUnionGroups * 16 / s.G : 0;
-    const size_t llds = static_cast<size_t>(4) * s.C * D * 2 +
-                        (static_cast<size_t>(2) * mw + kUnionMaxU + static_cast<size_t>(lT) * (kUnionMaxU / 32)) * 4;
-    if (local && s.G > 1 && union_ok(s) && llds <= kUnionMaxLds && row0 % lT == 0) {
+    // union kernel did not take go through the row-tile kernel of
+    // attn_tiles.hip: the forced blocks staged once per tile for every head,
+    // then the far partials merged.
+    if (a.tile_order) {
       ProfScope ps("attn_local", st);
-      const int ltiles = (row0 + nrows + lT - 1) / lT - row0 / lT;
-      const int lcount = s.BH() * ltiles;
-      const uint16_t* qq = static_cast<const uint16_t*>(q);
-      const uint16_t* kk = static_cast<const uint16_t*>(k);
-      const uint16_t* vv = static_cast<const uint16_t*>(v);
-      auto go = [&](auto kern) {
-        if (llds > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(llds));
-        int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kLocalWaves * 64, llds) != hipSuccess ||
-            per_cu < 1)
-          per_cu = 1;
-        const unsigned lgrid = static_cast<unsigned>(std::min(lcount, per_cu * kDeviceCUs));
-        kern<<<lgrid, kLocalWaves * 64, llds, st>>>(a, qq, kk, vv, idx, static_cast<uint16_t*>(o), lse, nullptr,
-                                                    nullptr, part_o, part_lse, ltiles, lcount);
-      };
-      auto by_g = [&](auto k2, auto k4, auto k8, auto k16) {
-        switch (s.G) {
-          case 2: go(k2); break;
-          case 4: go(k4); break;
-          case 8: go(k8); break;
-          default: go(k16); break;
-        }
-      };
-#define PISA_LOCAL(CT) \
-      by_g(attn_union_kernel<D, CT, 2, true>, attn_union_kernel<D, CT, 4, true>, attn_union_kernel<D, CT, 8, true>, \
-           attn_union_kernel<D, CT, 16, true>)
-      if (s.C == 32) PISA_LOCAL(1);
-      else if (s.C == 64) PISA_LOCAL(2);
-      else if (s.C == 96) PISA_LOCAL(3);
-      else PISA_LOCAL(4);
-#undef PISA_LOCAL
+      e = launch_attn_tiles(a, s.BH(), D, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                            static_cast<const uint16_t*>(v), idx, static_cast<uint16_t*>(o), lse, part_o, part_lse,
+                            st);
+      if (e != hipSuccess) return e;
     } else if (local) {
       ProfScope ps("attn_local", st);
       const int tq0 = s.N - s.Nq;

@@ -66,15 +66,24 @@ size_t cluster_ws(int BH, int M1, int64_t max_pairs, int max_rows);
 // Chunk w of the cluster list when the consumer takes up to `tile` pairs per
 // workgroup (the tile offsets of launch_cluster(..., tile)): its cluster (the
 // largest cl with toffs[cl] <= w) and pair range; false past the last chunk.
+// Every lane of every wavefront calls it with the same w: the 64 lanes probe
+// 64 places at once, so that a workgroup waits for 3 dependent loads among
+// 8192 clusters where a binary search waits for 13.
 __device__ __forceinline__ bool cluster_chunk(const int32_t* __restrict__ offs, const int32_t* __restrict__ toffs,
                                               int64_t ncl, int64_t w, int tile, int64_t& cl, int& beg, int& end) {
+  const int lane = threadIdx.x & 63;
   if (w >= toffs[ncl]) return false;
-  int64_t lo = 0, hi = ncl - 1;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) >> 1;
-    if (toffs[mid] <= w) lo = mid; else hi = mid - 1;
+  int64_t lo = 0, n = ncl;  // the answer is among [lo, lo + n)
+  while (n > 64) {
+    const int64_t step = (n + 63) >> 6;
+    const int64_t p = lo + lane * step;
+    const uint64_t m = __ballot(p < lo + n && toffs[p < lo + n ? p : lo] <= w);
+    const int64_t at = lo + (__popcll(m) - 1) * step;
+    n = min(step, lo + n - at);
+    lo = at;
   }
-  cl = lo;
+  const uint64_t m = __ballot(lane < n && toffs[lane < n ? lo + lane : lo] <= w);
+  cl = lo + __popcll(m) - 1;
   beg = offs[cl] + static_cast<int>(w - toffs[cl]) * tile;
   end = min(offs[cl + 1], beg + tile);
   return true;
