@@ -109,15 +109,6 @@ __device__ __forceinline__ void load_row_part<float, 4>(const float* __restrict_
   x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
 }
 
-// Sum over the 16 lanes of a lane group (lanes 16j .. 16j+15).
-__device__ __forceinline__ float sum16(float v) {
-  v += __shfl_xor(v, 8, 16);
-  v += __shfl_xor(v, 4, 16);
-  v += __shfl_xor(v, 2, 16);
-  v += __shfl_xor(v, 1, 16);
-  return v;
-}
-
 // ---- cross-lane moves on the VALU (DPP) or the LDS swizzle unit -------------
 // dpp_ctrl encodings: quad_perm 0x00-0xFF, row_shr:n 0x110+n, row_ror:n
 // 0x120+n, row_bcast15 0x142.  Lanes without a source (or masked rows) read 0.
@@ -128,6 +119,15 @@ __device__ __forceinline__ int dpp_i(int v) {
 template <int CTRL, int ROW_MASK = 0xF>
 __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, dpp_i<CTRL, ROW_MASK>(__builtin_bit_cast(int, v)));
+}
+
+// Sum over the 16 lanes of a lane group (lanes 16j .. 16j+15), in every lane.
+__device__ __forceinline__ float sum16(float v) {
+  v += dpp_f<0x128>(v);  // row_ror:8
+  v += dpp_f<0x124>(v);  // row_ror:4
+  v += dpp_f<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_f<0xB1>(v);   // quad_perm [1,0,3,2]
+  return v;
 }
 
 // Sum over each 16-lane row; the total lands in lane 15 of the row.
