@@ -184,8 +184,14 @@ int pick_schedule(const pisa_problem* p, const pisa::Shape& s, const pisa::Geo& 
 
 size_t select_ws(int sched, const pisa::Shape& s, const pisa::Geo& g) {
   if (sched == PISA_SCHEDULE_TWO_STAGE) return pisa::select_two_stage_ws(s, g);
-  if (sched == PISA_SCHEDULE_SPLIT) return pisa::select_split_ws(s);
+  if (sched == PISA_SCHEDULE_SPLIT) return pisa::select_split_ws(s, g);
   return 0;
+}
+
+// The workspace that the call insists on (a split selection is faster with
+// all of select_ws()).
+size_t select_ws_min(int sched, const pisa::Shape& s, const pisa::Geo& g) {
+  return sched == PISA_SCHEDULE_SPLIT ? pisa::select_split_ws_min(s) : select_ws(sched, s, g);
 }
 
 #define PISA_TRY(x)           \
@@ -214,13 +220,13 @@ int check_select(const pisa_problem* p, const void* q, const void* k, const floa
 }
 
 int run_select(const pisa::Shape& s, const pisa::Geo& g, int sched, const void* q, const void* k,
-               const float* pyramid, int32_t* block_idx, float* block_score, void* ws, hipStream_t st,
-               const char* who) {
+               const float* pyramid, int32_t* block_idx, float* block_score, void* ws, size_t ws_bytes,
+               hipStream_t st, const char* who) {
   hipError_t e;
   if (sched == PISA_SCHEDULE_TWO_STAGE)
     e = pisa::launch_select_two_stage(s, g, q, k, pyramid, block_idx, block_score, ws, st);
   else if (sched == PISA_SCHEDULE_SPLIT)
-    e = pisa::launch_select_split(s, g, q, k, pyramid, block_idx, block_score, ws, st);
+    e = pisa::launch_select_split(s, g, q, k, pyramid, block_idx, block_score, ws, ws_bytes, st);
   else
     e = pisa::launch_select_fused(s, g, q, k, pyramid, block_idx, block_score, st);
   return device_status(e, who);
@@ -411,8 +417,8 @@ int pisa_select(const pisa_problem* p, const void* q, const void* k, const float
   pisa::Geo g{};
   int sched = 0;
   PISA_TRY(check_select(p, q, k, pyramid, block_idx, block_score, &s, &g, &sched));
-  PISA_TRY(check_ws(ws, ws_bytes, select_ws(sched, s, g)));
-  return run_select(s, g, sched, q, k, pyramid, block_idx, block_score, ws, static_cast<hipStream_t>(stream),
+  PISA_TRY(check_ws(ws, ws_bytes, select_ws_min(sched, s, g)));
+  return run_select(s, g, sched, q, k, pyramid, block_idx, block_score, ws, ws_bytes, static_cast<hipStream_t>(stream),
                     "pisa_select");
 }
 
@@ -422,7 +428,7 @@ int pisa_select_static(const pisa_problem* p, const void* q, const void* k, cons
   pisa::Geo g{};
   int sched = 0;
   PISA_TRY(check_select(p, q, k, pyramid, block_idx, block_score, &s, &g, &sched));
-  const size_t need = select_ws(sched, s, g);
+  const size_t need = select_ws_min(sched, s, g);
   if (need > PISA_STATIC_SCRATCH_BYTES)
     return fail(PISA_ERR_WORKSPACE,
                 "pisa_select_static: this selection needs %zu bytes of scratch, the static scratch holds %zu "
@@ -430,8 +436,8 @@ int pisa_select_static(const pisa_problem* p, const void* q, const void* k, cons
                 need, static_cast<size_t>(PISA_STATIC_SCRATCH_BYTES));
   void* ws = nullptr;
   if (need > 0) PISA_TRY(static_scratch(&ws));
-  return run_select(s, g, sched, q, k, pyramid, block_idx, block_score, ws, static_cast<hipStream_t>(stream),
-                    "pisa_select_static");
+  return run_select(s, g, sched, q, k, pyramid, block_idx, block_score, ws, PISA_STATIC_SCRATCH_BYTES,
+                    static_cast<hipStream_t>(stream), "pisa_select_static");
 }
 
 int pisa_select_flat_bsa(const pisa_problem* p, const void* q, const float* pyramid, int32_t* block_idx, void* ws,

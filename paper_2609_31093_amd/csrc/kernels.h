@@ -118,10 +118,12 @@ hipError_t launch_cache_grow(const GrowArgs& a, int BH, const float* pyr_old, fl
 hipError_t launch_select_fused(const Shape& s, const Geo& geo, const void* q, const void* k,
                                const float* pyr, int32_t* idx, float* score, hipStream_t st);
 
-// Split selector for few rows (decode): workspace of select_split_ws().
-size_t select_split_ws(const Shape& s);
+// Split selector for few rows (decode): a workspace of select_split_ws()
+// bytes; with select_split_ws_min() it runs too, level by level.
+size_t select_split_ws(const Shape& s, const Geo& geo);
+size_t select_split_ws_min(const Shape& s);
 hipError_t launch_select_split(const Shape& s, const Geo& geo, const void* q, const void* k, const float* pyr,
-                               int32_t* idx, float* score, void* ws, hipStream_t st);
+                               int32_t* idx, float* score, void* ws, size_t ws_bytes, hipStream_t st);
 
 // Two-stage selector: workspace layout is computed by select_two_stage_ws().
 size_t select_two_stage_ws(const Shape& s, const Geo& geo);

@@ -46,6 +46,10 @@ struct SelArgs {
   int H, Hkv, G, Nq, K, causal, gK;
   int score_kind;   // kScoreLse / kScoreMean / kScoreMeanVar
   float qscale2;    // log2(e) / sqrt(d)
+  // split schedule with every node scored up front: the scores [row][ns_stride]
+  // of levels 2 .. ns_top, levels one after another
+  float* ns;
+  int ns_total, ns_stride, ns_top;
 };
 
 struct TopkArgsP {
@@ -2458,6 +2462,136 @@ __global__ __launch_bounds__(256) void stage1_row_kernel(SelArgs a) {
 }
 
 // ----------------------------------------------------------------------------
+// Few rows (decode) over a pyramid that the whole device reads in one go: the
+// score of every node that could be ranked, 16 lanes per node, and then the
+// walk down the levels from those scores alone (walk_levels, by a wavefront of
+// each leaf-scoring workgroup).  The walk level by level waits for memory once
+// per level on one workgroup per row; here it waits twice in all, for the price
+// of reading the pyramid, about 5 us for the 16 MB of 8 heads at 131072 tokens.
+// ----------------------------------------------------------------------------
+template <typename T, int D, int GMAX>
+__global__ __launch_bounds__(256) void node_score_kernel(SelArgs a) {
+  constexpr int DPL = D / 16;
+  const Geo& geo = a.geo;
+  const int g = geo.g, G = a.G;
+  const int grp = threadIdx.x >> 4, sub = threadIdx.x & 15;
+  const int64_t rg = blockIdx.y;  // bh * Nq + row
+  const int bh = static_cast<int>(rg / a.Nq), row = static_cast<int>(rg - static_cast<int64_t>(bh) * a.Nq);
+  const int b = bh / a.Hkv, h = bh - b * a.Hkv;
+  const int n = blockIdx.x * 16 + grp;
+  const int nc = min(n, a.ns_total - 1);
+  // the node's level and place
+  int node = 0, mb = 1;
+  int64_t off = 0;
+  int base = 0;
+  for (int lev = 2; lev <= a.ns_top; ++lev) {
+    if (nc >= base) {
+      node = nc - base;
+      mb = geo.M[lev - 1];
+      off = geo.off[lev - 1];
+    }
+    base += geo.M[lev];
+  }
+  const int c0 = node * g, nch = min(g, mb - c0);
+  const float* pbase = a.pyr + (static_cast<int64_t>(bh) * geo.R + off + c0) * D + sub * DPL;
+  float qv[GMAX][DPL];
+  ScoreAcc st[GMAX];
+  for (int j = 0; j < nch; j += 2) {  // two children at a time
+    float x[2][DPL];
+    load_row_part<float, DPL>(pbase + static_cast<int64_t>(j) * D, x[0]);
+    load_row_part<float, DPL>(pbase + static_cast<int64_t>(min(j + 1, nch - 1)) * D, x[1]);
+    if (j == 0) {  // the query with the first children
+      const T* qb = static_cast<const T*>(a.q);
+#pragma unroll
+      for (int hh = 0; hh < GMAX; ++hh) {
+        st[hh] = acc_empty(a.score_kind);
+#pragma unroll
+        for (int e = 0; e < DPL; ++e) qv[hh][e] = 0.f;
+        if (hh < G) {
+          load_row_part<T, DPL>(qb + ((static_cast<int64_t>(b) * a.H + h * G + hh) * a.Nq + row) * D + sub * DPL, qv[hh]);
+#pragma unroll
+          for (int e = 0; e < DPL; ++e) qv[hh][e] *= a.qscale2;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (j + u < nch) {
+#pragma unroll
+        for (int hh = 0; hh < GMAX; ++hh) {
+          if (hh < G) {
+            float d0 = 0.f;
+#pragma unroll
+            for (int i = 0; i < DPL; ++i) d0 = fmaf(qv[hh][i], x[u][i], d0);
+            acc_push(a.score_kind, st[hh], sum16(d0));
+          }
+        }
+      }
+    }
+  }
+  float u = 0.f;
+#pragma unroll
+  for (int hh = 0; hh < GMAX; ++hh) {
+    if (hh < G) u += acc_value(a.score_kind, st[hh]);
+  }
+  if (sub == 0 && n < a.ns_total) a.ns[rg * a.ns_stride + n] = u;
+}
+
+// One wavefront's walk from the first ranked level down to the leaf candidates
+// (g*K <= 64), scores from LDS; returns their number, and lane i's in
+// ascending order.
+__device__ __forceinline__ int walk_levels(const SelArgs& a, int c, int lane, const float* sc, int* s_cand, int& leaf) {
+  const Geo& geo = a.geo;
+  const int g = geo.g, K = a.K;
+  auto n_eligible = [&](int lev) { return a.causal ? min(anc_at(geo, c, lev) + 1, geo.M[lev]) : geo.M[lev]; };
+  int start = 1;
+  for (int lev = a.ns_top; lev >= 2; --lev) {
+    if (n_eligible(lev) > K) {
+      start = lev;
+      break;
+    }
+  }
+  int nA = n_eligible(start);
+  int node = lane < nA ? lane : -1;
+  int base = 0;  // of level lev's scores
+  for (int lev = 2; lev < start; ++lev) base += geo.M[lev];
+  for (int lev = start; lev >= 2; --lev) {
+    const Forced fz = forced_at(geo, lev, c, a.causal);
+    const bool valid = node >= 0, ranked = nA > K;
+    float key = valid ? INFINITY : -INFINITY;
+    if (ranked && valid && !fz.is(node)) key = sc[base + node];
+    int knode = node;
+    bool kept = valid;
+    if (ranked) {
+      int pack = valid ? node : 0x7FFFFFC0 | lane;
+      if (a.gK <= 32)
+        sort32_top16(key, pack, lane & 31, K != 16);
+      else
+        sort64(key, pack, lane);
+      kept = lane < K && key != -INFINITY;
+      knode = pack;
+    }
+    const int rmax = a.causal ? min(anc_at(geo, c, lev - 1), geo.M[lev - 1] - 1) : geo.M[lev - 1] - 1;
+    const int c0 = knode * g;
+    const int nk = kept ? max(0, min(c0 + g - 1, rmax) - c0 + 1) : 0;
+    const int incl = scan64_incl(nk, lane);
+    nA = __builtin_amdgcn_readlane(incl, 63);
+    for (int j = 0; j < nk; ++j) s_cand[incl - nk + j] = c0 + j;
+    wave_sync();
+    node = lane < nA ? s_cand[lane] : -1;
+    wave_sync();
+    if (lev > 2) base -= geo.M[lev - 1];
+  }
+  float akey = node >= 0 ? -static_cast<float>(node) : -INFINITY;
+  leaf = node >= 0 ? node : 0x7FFFFFC0 | lane;
+  if (a.gK <= 32)
+    sort32(akey, leaf, lane & 31);
+  else
+    sort64(akey, leaf, lane);
+  return nA;
+}
+
+// ----------------------------------------------------------------------------
 // Leaf scoring for few rows (decode): one workgroup per (row, candidate slot)
 // computes the exact LSE over the candidate block's raw keys for the G query
 // heads of the KV head (Sec. 3.3 leaf level; the same u as the clustered
@@ -2465,7 +2599,80 @@ __global__ __launch_bounds__(256) void stage1_row_kernel(SelArgs a) {
 // step costs a few memory round trips whatever the number of rows; key-block
 // reuse across queries, the reason for clustering, does not arise here.
 // ----------------------------------------------------------------------------
-template <typename T, int D, int GMAX>
+// The same walk for 64 < g*K <= 128: two candidates per lane, ranked as in
+// select_kernel, the lists in LDS (list: [128], ascending all the way down;
+// flag: [128], next: [128]).  Returns their number.
+__device__ __forceinline__ int walk_levels128(const SelArgs& a, int c, int lane, const float* sc, int* list, int* flag,
+                                              int* next) {
+  const Geo& geo = a.geo;
+  const int g = geo.g, K = a.K;
+  auto n_eligible = [&](int lev) { return a.causal ? min(anc_at(geo, c, lev) + 1, geo.M[lev]) : geo.M[lev]; };
+  int start = 1;
+  for (int lev = a.ns_top; lev >= 2; --lev) {
+    if (n_eligible(lev) > K) {
+      start = lev;
+      break;
+    }
+  }
+  int nA = n_eligible(start);  // at most g*K: a level up holds at most K
+  for (int ci = lane; ci < nA; ci += 64) list[ci] = ci;
+  int base = 0;  // of level lev's scores
+  for (int lev = 2; lev < start; ++lev) base += geo.M[lev];
+  wave_sync();
+  for (int lev = start; lev >= 2; --lev) {
+    const Forced fz = forced_at(geo, lev, c, a.causal);
+    if (nA > K) {
+      const int keepn = K - fz.count();
+      uint32_t khi[2], klo[2];
+      int nforced = 0;
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const int ci = lane + 64 * s2;
+        const bool v = ci < nA;
+        const int node = v ? list[ci] : 0;
+        const bool f = v && fz.is(node);
+        khi[s2] = !v ? 0xFFFFFFFFu : (f ? 0u : desc_bits(sc[base + node]));
+        klo[s2] = static_cast<uint32_t>(ci);
+        nforced += __popcll(__ballot(f));
+      }
+      sort128(khi, klo, lane);
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2) {
+        const int rk = lane + 64 * s2;
+        if (static_cast<int>(klo[s2]) < nA) flag[klo[s2]] = (rk < nforced || rk - nforced < keepn) ? 1 : 0;
+      }
+    } else {
+      for (int ci = lane; ci < nA; ci += 64) flag[ci] = 1;
+    }
+    wave_sync();
+    const int rmax = a.causal ? min(anc_at(geo, c, lev - 1), geo.M[lev - 1] - 1) : geo.M[lev - 1] - 1;
+    const int i0 = lane * 2, i1 = min(nA, i0 + 2);
+    int mine = 0;
+    for (int ci = i0; ci < i1; ++ci) {
+      if (flag[ci]) mine += max(0, min(list[ci] * g + g - 1, rmax) - list[ci] * g + 1);
+    }
+    int pos = scan64_incl(mine, lane);
+    const int total = __builtin_amdgcn_readlane(pos, 63);
+    pos -= mine;
+    for (int ci = i0; ci < i1; ++ci) {
+      if (flag[ci]) {
+        const int c0 = list[ci] * g;
+        const int n = max(0, min(c0 + g - 1, rmax) - c0 + 1);
+        for (int j = 0; j < n; ++j) next[pos++] = c0 + j;
+      }
+    }
+    wave_sync();
+    nA = total;
+    for (int ci = lane; ci < nA; ci += 64) list[ci] = next[ci];
+    wave_sync();
+    if (lev > 2) base -= geo.M[lev - 1];
+  }
+  return nA;
+}
+
+// WALK: the candidates come from the node scores (every workgroup of a row
+// walks for itself; the first one stores the list for the final Top-K).
+template <typename T, int D, int GMAX, bool WALK>
 __global__ __launch_bounds__(256) void leaf_slot_kernel(SelArgs a, const int32_t* __restrict__ a1,
                                                         const int32_t* __restrict__ a1cnt, float* __restrict__ u1) {
   constexpr int DPL = D / 16;
@@ -2481,8 +2688,11 @@ __global__ __launch_bounds__(256) void leaf_slot_kernel(SelArgs a, const int32_t
   const int tid = threadIdx.x, grp = tid >> 4, sub = tid & 15;
   // the candidate count, the slot's node (in bounds: slot < g*K) and q are
   // requested together
-  const int n = a1cnt[rg];
-  const int node = a1[rg * a.gK + slot];
+  int n = 0, node = 0;
+  if constexpr (!WALK) {
+    n = a1cnt[rg];
+    node = a1[rg * a.gK + slot];
+  }
   float qv[GMAX][DPL];
   {
     const T* qb = static_cast<const T*>(a.q);
@@ -2499,8 +2709,36 @@ __global__ __launch_bounds__(256) void leaf_slot_kernel(SelArgs a, const int32_t
       }
     }
   }
-  if (slot >= n || n <= a.K) return;
   const int c = (geo.N - a.Nq + row) / geo.C;
+  if constexpr (WALK) {
+    extern __shared__ __align__(16) float s_sc[];  // [ns_stride] the row's node scores
+    __shared__ int s_list[3 * 128];
+    __shared__ int s_n;
+    const float* src = a.ns + rg * a.ns_stride;
+    for (int i = tid * 4; i < a.ns_total; i += 1024)
+      *reinterpret_cast<float4*>(s_sc + i) = *reinterpret_cast<const float4*>(src + i);
+    __syncthreads();
+    if (tid < 64) {
+      int nA;
+      if (a.gK <= 64) {
+        int leaf;
+        nA = walk_levels(a, c, tid, s_sc, s_list + 128, leaf);
+        s_list[tid] = leaf;
+      } else {
+        nA = walk_levels128(a, c, tid, s_sc, s_list, s_list + 128, s_list + 256);
+      }
+      wave_sync();
+      if (slot == 0) {
+        for (int i = tid; i < a.gK; i += 64) a.a1[rg * a.gK + i] = i < nA ? s_list[i] : -1;
+        if (tid == 0) a.a1cnt[rg] = nA;
+      }
+      if (tid == 0) s_n = nA;
+    }
+    __syncthreads();
+    n = s_n;
+    node = s_list[slot];
+  }
+  if (slot >= n || n <= a.K) return;
   if (a.causal && (node == 0 || node == c || node == c - 1)) return;  // forced: never scored
   const int r0 = node * geo.C;
   const int nrows = min(geo.C, geo.N - r0);
@@ -2931,6 +3169,43 @@ hipError_t launch_select_two_stage(const Shape& s, const Geo& geo, const void* q
 
 // Split schedule: stage 1 with a workgroup per row, every scored leaf
 // candidate on a workgroup of its own, then the final Top-K.
+// Node scores up front: the ranked levels' nodes (levels 2 .. top with more
+// than K of them) as one list per row, when
+//   * at least two levels are ranked (with one, the walk waits once as well; but
+//     select_kernel, which takes g*K > 64 otherwise, waits longer);
+//   * the rows together read no more than kNodeScoreBytes of summaries for it
+//     (16 MB at 8 x 131072 tokens: 40.1 -> 35.9 us a step) and a row's scores
+//     fit 32 KiB of LDS;
+//   * at most kNodeScoreGroups leaf-scoring workgroups walk, 4 per CU (32 rows
+//     of 4 heads, 20011 tokens: 59.0 -> 51.9 us; 64 rows of one head, 16384
+//     tokens, where twice as many walk: 43.6 against 49.1); with g*K > 64,
+//     where the other path is select_kernel, four times that (2 rows, 524288
+//     tokens, 128-key blocks, g = 4, K = 32: 162 -> 53 us a step).
+constexpr int64_t kNodeScoreBytes = 32ll << 20;
+constexpr int kNodeScoreMax = 8192;
+constexpr int64_t kNodeScoreGroups = 1024;
+
+struct NodeScores {
+  int total, stride, top;
+};
+
+static NodeScores node_scores(const Shape& s, const Geo& geo) {
+  NodeScores n{0, 0, 1};
+  if (s.gK() > 128) return n;
+  int64_t total = 0;
+  for (int l = 2; l <= geo.L && geo.M[l] > s.K; ++l) {
+    total += geo.M[l];
+    n.top = l;
+  }
+  const int64_t bytes = static_cast<int64_t>(s.BH()) * s.Nq * total * s.g * s.D * 4;
+  if (n.top < (s.gK() > 64 ? 2 : 3) || total > kNodeScoreMax || bytes > kNodeScoreBytes ||
+      static_cast<int64_t>(s.BH()) * s.Nq * s.gK() > (s.gK() > 64 ? 4 : 1) * kNodeScoreGroups)
+    return NodeScores{0, 0, 1};
+  n.total = static_cast<int>(total);
+  n.stride = (n.total + 3) & ~3;
+  return n;
+}
+
 struct SplitWs {
   size_t a1, a1cnt, u1, total;
 };
@@ -2946,22 +3221,31 @@ static SplitWs split_layout(const Shape& s) {
   return w;
 }
 
-size_t select_split_ws(const Shape& s) { return split_layout(s).total; }
+size_t select_split_ws_min(const Shape& s) { return split_layout(s).total; }
 
-template <typename T, int D>
-static void launch_leaf_slot(const Shape& s, const SelArgs& a, const int32_t* a1, const int32_t* a1cnt, float* u1,
-                             hipStream_t st) {
-  dim3 grid(s.gK(), static_cast<unsigned>(static_cast<int64_t>(s.BH()) * s.Nq));
-  if (s.G == 1)
-    leaf_slot_kernel<T, D, 1><<<grid, 256, 0, st>>>(a, a1, a1cnt, u1);
-  else if (s.G <= 4)
-    leaf_slot_kernel<T, D, 4><<<grid, 256, 0, st>>>(a, a1, a1cnt, u1);
-  else
-    leaf_slot_kernel<T, D, 16><<<grid, 256, 0, st>>>(a, a1, a1cnt, u1);
+size_t select_split_ws(const Shape& s, const Geo& geo) {
+  return split_layout(s).total + align256(static_cast<size_t>(s.BH()) * s.Nq * node_scores(s, geo).stride * 4);
+}
+
+// f(type, head dim, GMAX) for the problem's.
+template <typename F>
+static void by_shape(const Shape& s, F&& f) {
+  using std::integral_constant;
+  auto by_g = [&](auto t, auto d) {
+    if (s.G == 1) f(t, d, integral_constant<int, 1>{});
+    else if (s.G <= 4) f(t, d, integral_constant<int, 4>{});
+    else f(t, d, integral_constant<int, 16>{});
+  };
+  auto by_d = [&](auto t) {
+    if (s.D == 128) by_g(t, integral_constant<int, 128>{});
+    else by_g(t, integral_constant<int, 64>{});
+  };
+  if (s.bf16) by_d(uint16_t{});
+  else by_d(float{});
 }
 
 hipError_t launch_select_split(const Shape& s, const Geo& geo, const void* q, const void* k, const float* pyr,
-                               int32_t* idx, float* score, void* ws, hipStream_t st) {
+                               int32_t* idx, float* score, void* ws, size_t ws_bytes, hipStream_t st) {
   const SplitWs w = split_layout(s);
   char* base = static_cast<char*>(ws);
   int32_t* a1 = reinterpret_cast<int32_t*>(base + w.a1);
@@ -2971,53 +3255,54 @@ hipError_t launch_select_split(const Shape& s, const Geo& geo, const void* q, co
   SelArgs a = make_sel_args(s, geo, q, k, pyr);
   a.a1 = a1;
   a.a1cnt = a1cnt;
-  {
-    ProfScope ps("select_stage1", st);
-    if (s.gK() <= 64) {
-      dim3 grid(s.Nq, s.BH());
-      const size_t lds = static_cast<size_t>(s.gK()) * s.g * s.G * sizeof(float);
-      auto go = [&](auto tag) {
-        using T = decltype(tag);
-        auto run = [&](auto kern) {
+  // (a caller that brings only the smaller workspace gets the walk level by level)
+  const NodeScores ns = ws_bytes >= select_split_ws(s, geo) ? node_scores(s, geo) : NodeScores{0, 0, 1};
+  const unsigned rows = static_cast<unsigned>(static_cast<int64_t>(s.BH()) * s.Nq);
+  if (ns.total > 0) {
+    a.ns = reinterpret_cast<float*>(base + w.total);
+    a.ns_total = ns.total;
+    a.ns_stride = ns.stride;
+    a.ns_top = ns.top;
+    {
+      ProfScope ps("select_stage1", st);
+      dim3 grid((ns.total + 15) / 16, rows);
+      by_shape(s, [&](auto t, auto d, auto gm) {
+        node_score_kernel<decltype(t), decltype(d)::value, decltype(gm)::value><<<grid, 256, 0, st>>>(a);
+      });
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    ProfScope ps("leaf_score", st);
+    dim3 grid(s.gK(), rows);
+    by_shape(s, [&](auto t, auto d, auto gm) {
+      leaf_slot_kernel<decltype(t), decltype(d)::value, decltype(gm)::value, true>
+          <<<grid, 256, static_cast<size_t>(ns.stride) * 4, st>>>(a, a1, a1cnt, u1);
+    });
+  } else {
+    {
+      ProfScope ps("select_stage1", st);
+      if (s.gK() <= 64) {
+        dim3 grid(s.Nq, s.BH());
+        const size_t lds = static_cast<size_t>(s.gK()) * s.g * s.G * sizeof(float);
+        by_shape(s, [&](auto t, auto d, auto gm) {
+          auto* kern = stage1_row_kernel<decltype(t), decltype(d)::value, decltype(gm)::value>;
           if (lds > 60000)  // beyond the default dynamic limit once the static arrays are added
             (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
           kern<<<grid, 256, lds, st>>>(a);
-        };
-        if (s.D == 128) {
-          if (s.G == 1) run(stage1_row_kernel<T, 128, 1>);
-          else if (s.G <= 4) run(stage1_row_kernel<T, 128, 4>);
-          else run(stage1_row_kernel<T, 128, 16>);
-        } else {
-          if (s.G == 1) run(stage1_row_kernel<T, 64, 1>);
-          else if (s.G <= 4) run(stage1_row_kernel<T, 64, 4>);
-          else run(stage1_row_kernel<T, 64, 16>);
-        }
-      };
-      if (s.bf16)
-        go(uint16_t{});
-      else
-        go(float{});
-    } else if (s.bf16) {
-      launch_sel_d<uint16_t, 256, false>(s, a, st);
-    } else {
-      launch_sel_d<float, 256, false>(s, a, st);
+        });
+      } else if (s.bf16) {
+        launch_sel_d<uint16_t, 256, false>(s, a, st);
+      } else {
+        launch_sel_d<float, 256, false>(s, a, st);
+      }
     }
-  }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  {
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     ProfScope ps("leaf_score", st);
-    if (s.bf16) {
-      if (s.D == 128)
-        launch_leaf_slot<uint16_t, 128>(s, a, a1, a1cnt, u1, st);
-      else
-        launch_leaf_slot<uint16_t, 64>(s, a, a1, a1cnt, u1, st);
-    } else {
-      if (s.D == 128)
-        launch_leaf_slot<float, 128>(s, a, a1, a1cnt, u1, st);
-      else
-        launch_leaf_slot<float, 64>(s, a, a1, a1cnt, u1, st);
-    }
+    dim3 grid(s.gK(), rows);
+    by_shape(s, [&](auto t, auto d, auto gm) {
+      leaf_slot_kernel<decltype(t), decltype(d)::value, decltype(gm)::value, false>
+          <<<grid, 256, 0, st>>>(a, a1, a1cnt, u1);
+    });
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_final_topk(s, a1, a1cnt, u1, idx, score, st);
