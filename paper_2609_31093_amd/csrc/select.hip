@@ -883,11 +883,54 @@ __global__ __launch_bounds__(kMfmaSelRows * 64) void stage1_mfma_kernel(SelArgs 
 // place in it is the population count below its bit.  Products, scores,
 // ranking and expansion are otherwise those of stage1_mfma_kernel.
 constexpr int kUnionRows = 4;   // query rows per wavefront
-constexpr int kUnionWaves = 4;  // wavefronts per workgroup
+constexpr int kUnionWaves = 2;  // wavefronts per workgroup
 
-// LDS words of one wavefront of stage1_union_kernel.
+// LDS words of one wavefront of stage1_union_kernel: node lists in 16 bits
+// (a level above the leaves has fewer than 65536 nodes), flags in 8, the next
+// candidates over the scores they come after, so that seven workgroups fit a
+// CU (with 32-bit lists apart from each other eight wavefronts fitted; with
+// the rows' sorts side by side as well, 2 x 524288 rows of 4 heads, 128
+// candidates: 17.1 -> 13.8 ms).
 __host__ __device__ constexpr int union_wave_words(int bm_words) {
-  return kUnionRows * 128 * 3 + kUnionRows * 128 + kUnionRows * 128 * kUnionRows + 2 * (bm_words + 1);
+  return (kUnionRows * 128 * 2 + kUnionRows * 128 + kUnionRows * 128 * 2 + kUnionRows * 128 * kUnionRows * 4) / 4 +
+         ((2 * (bm_words + 1) + 3) & ~3);
+}
+
+// sort128 of R rows' entries side by side: independent chains, so that one
+// row's lane exchanges overlap the others' (one row after another, a
+// wavefront waited out each of the 28 steps four times).
+template <int R, int K2, int J>
+__device__ __forceinline__ void sort128_rows_stage(uint32_t (&hi)[R][2], uint32_t (&lo)[R][2]) {
+  if constexpr (J == 64) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint64_t x = (static_cast<uint64_t>(hi[r][0]) << 32) | lo[r][0];
+      const uint64_t y = (static_cast<uint64_t>(hi[r][1]) << 32) | lo[r][1];
+      const bool sw = y < x;
+      const uint32_t h0 = sw ? hi[r][1] : hi[r][0], l0 = sw ? lo[r][1] : lo[r][0];
+      hi[r][1] = sw ? hi[r][0] : hi[r][1];
+      lo[r][1] = sw ? lo[r][0] : lo[r][1];
+      hi[r][0] = h0;
+      lo[r][0] = l0;
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < R; ++r) sort128_half_step<K2, J, 0>(hi[r][0], lo[r][0]);
+#pragma unroll
+    for (int r = 0; r < R; ++r) sort128_half_step<K2, J, 1>(hi[r][1], lo[r][1]);
+  }
+  if constexpr (J > 1) sort128_rows_stage<R, K2, J / 2>(hi, lo);
+}
+
+template <int R>
+__device__ __forceinline__ void sort128_rows(uint32_t (&hi)[R][2], uint32_t (&lo)[R][2]) {
+  sort128_rows_stage<R, 2, 1>(hi, lo);
+  sort128_rows_stage<R, 4, 2>(hi, lo);
+  sort128_rows_stage<R, 8, 4>(hi, lo);
+  sort128_rows_stage<R, 16, 8>(hi, lo);
+  sort128_rows_stage<R, 32, 16>(hi, lo);
+  sort128_rows_stage<R, 64, 32>(hi, lo);
+  sort128_rows_stage<R, 128, 64>(hi, lo);
 }
 
 template <int D, int GC, int KIND>
@@ -905,12 +948,12 @@ __global__ __launch_bounds__(kUnionWaves * 64) void stage1_union_kernel(SelArgs 
   const int row0 = (blockIdx.x * kUnionWaves + wave) * R;
   if (row0 >= a.Nq) return;  // the whole wavefront leaves; only wavefront-level syncs follow
   int* L = lds_u + wave * union_wave_words(bm_words);
-  int* cand = L;                     // [R][128]
-  int* cand2 = cand + R * 128;       // [R][128]
-  int* flag = cand2 + R * 128;       // [R][128]
-  int* U = flag + R * 128;           // [UMAX] union, ascending
-  float* us = reinterpret_cast<float*>(U + UMAX);  // [UMAX][R] scores of the union for each row
-  uint32_t* bm = reinterpret_cast<uint32_t*>(us + UMAX * R);  // [bm_words + 1]
+  float* us = reinterpret_cast<float*>(L);                    // [UMAX][R] scores of the union for each row
+  uint16_t* cand2 = reinterpret_cast<uint16_t*>(L);           // [R][128] next candidates (the scores are used up)
+  uint16_t* cand = reinterpret_cast<uint16_t*>(us + UMAX * R);  // [R][128]
+  uint16_t* U = cand + R * 128;                               // [UMAX] union, ascending
+  uint8_t* flag = reinterpret_cast<uint8_t*>(U + UMAX);       // [R][128]
+  uint32_t* bm = reinterpret_cast<uint32_t*>(flag + R * 128); // [bm_words + 1]
   int* pre = reinterpret_cast<int*>(bm + bm_words + 1);       // [bm_words + 1]
   const int bh = blockIdx.y;
   const int b = bh / a.Hkv, h = bh - b * a.Hkv;
@@ -974,7 +1017,7 @@ __global__ __launch_bounds__(kUnionWaves * 64) void stage1_union_kernel(SelArgs 
         pre[w] = pos;
         uint32_t bits = bm[w];
         while (bits) {
-          U[pos++] = w * 32 + __ffs(bits) - 1;
+          U[pos++] = static_cast<uint16_t>(w * 32 + __ffs(bits) - 1);
           bits &= bits - 1;
         }
       }
@@ -1026,46 +1069,58 @@ __global__ __launch_bounds__(kUnionWaves * 64) void stage1_union_kernel(SelArgs 
       // 3) each ranked row ranks its own candidates with the union's scores:
       // forced first, then score descending, ties by candidate index
       // (ascending nodes), then empty slots
+      auto score_of = [&](int r, int node) {
+        const int w = node >> 5;
+        const int ui = pre[w] + __popc(bm[w] & ((1u << (node & 31)) - 1u));
+        return us[ui * R + r];
+      };
+      bool wide = false;
 #pragma unroll
-      for (int r = 0; r < R; ++r) {
-        if (!rk[r]) continue;
-        const Forced fz = forced_at(geo, lev, cr[r], a.causal);
-        const int keepn = K - fz.count();
-        const int nA = nAr[r];
-        const int* cr_ = cand + r * 128;
-        auto score_of = [&](int node) {
-          const int w = node >> 5;
-          const int ui = pre[w] + __popc(bm[w] & ((1u << (node & 31)) - 1u));
-          return us[ui * R + r];
-        };
-        int* fl = flag + r * 128;
-        if (nA <= 32) {
-          const bool v = lane < nA;
-          const int node = v ? cr_[lane] : 0;
+      for (int r = 0; r < R; ++r) wide = wide || (rk[r] && nAr[r] > 32);
+      if (!wide) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (!rk[r]) continue;
+          const Forced fz = forced_at(geo, lev, cr[r], a.causal);
+          const int keepn = K - fz.count();
+          const bool v = lane < nAr[r];
+          const int node = v ? cand[r * 128 + lane] : 0;
           const bool f = v && fz.is(node);
-          float key = !v ? -INFINITY : (f ? INFINITY : score_of(node));
+          float key = !v ? -INFINITY : (f ? INFINITY : score_of(r, node));
           int pack = lane;
           const int nforced = __popcll(__ballot(f));
           sort32(key, pack, lane & 31);
-          if (lane < nA) fl[pack] = (lane < nforced || lane - nforced < keepn) ? 1 : 0;
-        } else {
-          uint32_t khi[2], klo[2];
-          int nforced = 0;
+          if (lane < nAr[r]) flag[r * 128 + pack] = (lane < nforced || lane - nforced < keepn) ? 1 : 0;
+        }
+      } else {
+        uint32_t khi[R][2], klo[R][2];
+        int nforced[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const Forced fz = forced_at(geo, lev, cr[r], a.causal);
+          nforced[r] = 0;
 #pragma unroll
           for (int s2 = 0; s2 < 2; ++s2) {
             const int ci = lane + 64 * s2;
-            const bool v = ci < nA;
-            const int node = v ? cr_[ci] : 0;
+            const bool v = rk[r] && ci < nAr[r];
+            const int node = v ? cand[r * 128 + ci] : 0;
             const bool f = v && fz.is(node);
-            khi[s2] = !v ? 0xFFFFFFFFu : (f ? 0u : desc_bits(score_of(node)));
-            klo[s2] = static_cast<uint32_t>(ci);
-            nforced += __popcll(__ballot(f));
+            const float sc = v && !f ? score_of(r, node) : 0.f;
+            khi[r][s2] = !v ? 0xFFFFFFFFu : (f ? 0u : desc_bits(sc));
+            klo[r][s2] = static_cast<uint32_t>(ci);
+            nforced[r] += __popcll(__ballot(f));
           }
-          sort128(khi, klo, lane);
+        }
+        sort128_rows<R>(khi, klo);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (!rk[r]) continue;
+          const int keepn = K - forced_at(geo, lev, cr[r], a.causal).count();
 #pragma unroll
           for (int s2 = 0; s2 < 2; ++s2) {
             const int rk2 = lane + 64 * s2;
-            if (static_cast<int>(klo[s2]) < nA) fl[klo[s2]] = (rk2 < nforced || rk2 - nforced < keepn) ? 1 : 0;
+            if (static_cast<int>(klo[r][s2]) < nAr[r])
+              flag[r * 128 + klo[r][s2]] = (rk2 < nforced[r] || rk2 - nforced[r] < keepn) ? 1 : 0;
           }
         }
       }
@@ -1081,9 +1136,9 @@ __global__ __launch_bounds__(kUnionWaves * 64) void stage1_union_kernel(SelArgs 
     for (int r = 0; r < R; ++r) {
       if (!rv[r]) continue;
       const int rmax = a.causal ? min(anc_at(geo, cr[r], lev - 1), Mb - 1) : Mb - 1;
-      const int* cr_ = cand + r * 128;
-      const int* fl = flag + r * 128;
-      int* c2 = cand2 + r * 128;
+      const uint16_t* cr_ = cand + r * 128;
+      const uint8_t* fl = flag + r * 128;
+      uint16_t* c2 = cand2 + r * 128;
       const int i0 = lane * 2, i1 = min(nAr[r], i0 + 2);
       int mine = 0;
       for (int ci = i0; ci < i1; ++ci) {
@@ -1098,7 +1153,7 @@ __global__ __launch_bounds__(kUnionWaves * 64) void stage1_union_kernel(SelArgs 
         if (fl[ci]) {
           const int c0 = cr_[ci] * GC;
           const int n = max(0, min(c0 + GC - 1, rmax) - c0 + 1);
-          for (int jj = 0; jj < n; ++jj) c2[pos + jj] = c0 + jj;
+          for (int jj = 0; jj < n; ++jj) c2[pos + jj] = static_cast<uint16_t>(c0 + jj);
           pos += n;
         }
       }
