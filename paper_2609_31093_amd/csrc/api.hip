@@ -174,11 +174,28 @@ constexpr int kMaxClusterBins = 16384;
 // spreads each row's leaf candidates over workgroups of their own.
 constexpr int64_t kSplitMaxRows = 2048;
 
-int pick_schedule(const pisa_problem* p, const pisa::Shape& s, const pisa::Geo& g) {
+// Rows from which it groups the leaf pairs by key block: key-block reuse pays
+// once many queries share the key blocks (Sec. 3.3).  With up to four heads
+// per KV head from 2048 query rows of single heads on (one head: 8 x 256 rows
+// over 60000 keys 183 -> 145 us; four: 4 x 128 rows over 30000 keys 108 -> 94,
+// 2 x 256 rows with g*K = 128 over 200000 keys 446 -> 244; one head with 8 x
+// 128 rows: 114 against 120), with more above the split schedule's range (16
+// heads, 2 x 512 rows: 340 against 343 us; 2 x 1025 rows, where the fused
+// schedule served: 1230 -> 580).
+bool two_stage_pays(const pisa::Shape& s, int64_t rows) {
+  return s.G <= 4 ? rows * s.G >= kSplitMaxRows : rows > kSplitMaxRows;
+}
+
+// From this many rows the automatic schedule insists on the two-stage
+// workspace; below it a smaller one gets the other schedules.
+constexpr int64_t kTwoStageRows = 4096;
+
+// small_ws: the choice for a caller without the two-stage workspace.
+int pick_schedule(const pisa_problem* p, const pisa::Shape& s, const pisa::Geo& g, bool small_ws = false) {
   if (p->schedule != PISA_SCHEDULE_AUTO) return p->schedule;
   const int64_t rows = static_cast<int64_t>(s.Nq) * s.BH();
-  // Key-block reuse pays once many queries share the key blocks (Sec. 3.3).
-  if (s.bf16 && rows >= 4096 && g.M[1] <= kMaxClusterBins) return PISA_SCHEDULE_TWO_STAGE;
+  if (s.bf16 && g.M[1] <= kMaxClusterBins && (rows >= kTwoStageRows || (!small_ws && two_stage_pays(s, rows))))
+    return PISA_SCHEDULE_TWO_STAGE;
   return rows <= kSplitMaxRows ? PISA_SCHEDULE_SPLIT : PISA_SCHEDULE_FUSED;
 }
 
@@ -192,6 +209,13 @@ size_t select_ws(int sched, const pisa::Shape& s, const pisa::Geo& g) {
 // all of select_ws()).
 size_t select_ws_min(int sched, const pisa::Shape& s, const pisa::Geo& g) {
   return sched == PISA_SCHEDULE_SPLIT ? pisa::select_split_ws_min(s) : select_ws(sched, s, g);
+}
+
+// Settles the schedule for a workspace of ws_bytes, and how its stage 1 runs.
+int schedule_for_ws(const pisa_problem* p, pisa::Shape* s, const pisa::Geo& g, int sched, size_t ws_bytes) {
+  if (ws_bytes < select_ws_min(sched, *s, g)) sched = pick_schedule(p, *s, g, true);
+  s->plain_stage1 = p->schedule == PISA_SCHEDULE_AUTO && static_cast<int64_t>(s->Nq) * s->BH() < kTwoStageRows;
+  return sched;
 }
 
 #define PISA_TRY(x)           \
@@ -417,6 +441,7 @@ int pisa_select(const pisa_problem* p, const void* q, const void* k, const float
   pisa::Geo g{};
   int sched = 0;
   PISA_TRY(check_select(p, q, k, pyramid, block_idx, block_score, &s, &g, &sched));
+  sched = schedule_for_ws(p, &s, g, sched, ws ? ws_bytes : 0);
   PISA_TRY(check_ws(ws, ws_bytes, select_ws_min(sched, s, g)));
   return run_select(s, g, sched, q, k, pyramid, block_idx, block_score, ws, ws_bytes, static_cast<hipStream_t>(stream),
                     "pisa_select");
@@ -428,6 +453,7 @@ int pisa_select_static(const pisa_problem* p, const void* q, const void* k, cons
   pisa::Geo g{};
   int sched = 0;
   PISA_TRY(check_select(p, q, k, pyramid, block_idx, block_score, &s, &g, &sched));
+  sched = schedule_for_ws(p, &s, g, sched, PISA_STATIC_SCRATCH_BYTES);
   const size_t need = select_ws_min(sched, s, g);
   if (need > PISA_STATIC_SCRATCH_BYTES)
     return fail(PISA_ERR_WORKSPACE,

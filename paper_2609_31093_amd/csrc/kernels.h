@@ -30,6 +30,9 @@ struct Shape {
   int Nkv;    // rows per (batch, KV head) in k and v (row stride), >= N
   int score;  // PISA_SCORE_* reducer of the selection
   bool bf16;
+  // two-stage selection of fewer rows than the matrix-core stage 1 is meant
+  // for: the fp32 products of the split (up to 2048 rows) or fused schedules
+  bool plain_stage1 = false;
   int BH() const { return B * Hkv; }
   int gK() const { return g * K; }
 };

@@ -2997,6 +2997,42 @@ static hipError_t launch_final_topk(const Shape& s, const int32_t* a1, const int
   return hipGetLastError();
 }
 
+// f(type, head dim, GMAX) for the problem's.
+template <typename F>
+static void by_shape(const Shape& s, F&& f) {
+  using std::integral_constant;
+  auto by_g = [&](auto t, auto d) {
+    if (s.G == 1) f(t, d, integral_constant<int, 1>{});
+    else if (s.G <= 4) f(t, d, integral_constant<int, 4>{});
+    else f(t, d, integral_constant<int, 16>{});
+  };
+  auto by_d = [&](auto t) {
+    if (s.D == 128) by_g(t, integral_constant<int, 128>{});
+    else by_g(t, integral_constant<int, 64>{});
+  };
+  if (s.bf16) by_d(uint16_t{});
+  else by_d(float{});
+}
+
+// The intermediate levels on a workgroup per row.
+static void launch_stage1_rows(const Shape& s, const SelArgs& a, hipStream_t st) {
+  if (s.gK() <= 64) {
+    dim3 grid(s.Nq, s.BH());
+    const size_t lds = static_cast<size_t>(s.gK()) * s.g * s.G * sizeof(float);
+    by_shape(s, [&](auto t, auto d, auto gm) {
+      auto* kern = stage1_row_kernel<decltype(t), decltype(d)::value, decltype(gm)::value>;
+      if (lds > 60000)  // beyond the default dynamic limit once the static arrays are added
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+      kern<<<grid, 256, lds, st>>>(a);
+    });
+  } else if (s.bf16) {
+    launch_sel_d<uint16_t, 256, false>(s, a, st);
+  } else {
+    launch_sel_d<float, 256, false>(s, a, st);
+  }
+}
+
 static hipError_t launch_two_stage_heads(const Shape& s, const Geo& geo, const void* q, const void* k,
                                         const float* pyr, int32_t* idx, float* score, void* ws, hipStream_t st) {
   const TwoStageWs w = two_stage_layout(s, geo);
@@ -3013,7 +3049,9 @@ static hipError_t launch_two_stage_heads(const Shape& s, const Geo& geo, const v
   const bool narrow = s.gK() <= 32 && !stage1_mfma_ok(s);
   {
     ProfScope ps("select_stage1", st);
-    if (narrow) {
+    if (s.plain_stage1 && (!narrow || static_cast<int64_t>(s.BH()) * s.Nq <= 2048)) {
+      launch_stage1_rows(s, a, st);
+    } else if (narrow) {
       const int gK = s.gK();
       const int words = gK * s.g * 2 + gK + gK * s.g * s.G + gK * s.G;
       dim3 grid((s.Nq + 7) / 8, s.BH());
@@ -3282,23 +3320,6 @@ size_t select_split_ws(const Shape& s, const Geo& geo) {
   return split_layout(s).total + align256(static_cast<size_t>(s.BH()) * s.Nq * node_scores(s, geo).stride * 4);
 }
 
-// f(type, head dim, GMAX) for the problem's.
-template <typename F>
-static void by_shape(const Shape& s, F&& f) {
-  using std::integral_constant;
-  auto by_g = [&](auto t, auto d) {
-    if (s.G == 1) f(t, d, integral_constant<int, 1>{});
-    else if (s.G <= 4) f(t, d, integral_constant<int, 4>{});
-    else f(t, d, integral_constant<int, 16>{});
-  };
-  auto by_d = [&](auto t) {
-    if (s.D == 128) by_g(t, integral_constant<int, 128>{});
-    else by_g(t, integral_constant<int, 64>{});
-  };
-  if (s.bf16) by_d(uint16_t{});
-  else by_d(float{});
-}
-
 hipError_t launch_select_split(const Shape& s, const Geo& geo, const void* q, const void* k, const float* pyr,
                                int32_t* idx, float* score, void* ws, size_t ws_bytes, hipStream_t st) {
   const SplitWs w = split_layout(s);
@@ -3335,21 +3356,7 @@ hipError_t launch_select_split(const Shape& s, const Geo& geo, const void* q, co
   } else {
     {
       ProfScope ps("select_stage1", st);
-      if (s.gK() <= 64) {
-        dim3 grid(s.Nq, s.BH());
-        const size_t lds = static_cast<size_t>(s.gK()) * s.g * s.G * sizeof(float);
-        by_shape(s, [&](auto t, auto d, auto gm) {
-          auto* kern = stage1_row_kernel<decltype(t), decltype(d)::value, decltype(gm)::value>;
-          if (lds > 60000)  // beyond the default dynamic limit once the static arrays are added
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-          kern<<<grid, 256, lds, st>>>(a);
-        });
-      } else if (s.bf16) {
-        launch_sel_d<uint16_t, 256, false>(s, a, st);
-      } else {
-        launch_sel_d<float, 256, false>(s, a, st);
-      }
+      launch_stage1_rows(s, a, st);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     ProfScope ps("leaf_score", st);

@@ -61,3 +61,36 @@ def test_split_from_node_scores(shape):
 def test_small_workspace_is_smaller():
     p = pisa.make_problem(1, 2, 2, 1, 40000, 128, 64, 2, 16, 1, "bf16")
     assert pisa.pisa_select_workspace_bytes(p) > _small_ws(p)
+
+
+@pytest.mark.parametrize("shape", [
+    # (B, H, Hkv, Nq, N, d, C, g, K, causal): the automatic schedule's range between split and 4096 rows
+    (1, 4, 1, 512, 9001, 128, 64, 2, 16, 1),     # from 512 rows with four heads
+    (1, 1, 1, 2047, 6000, 64, 64, 2, 8, 1),      # one below, and at, the 2048 rows of single heads
+    (1, 1, 1, 2048, 6000, 64, 64, 2, 8, 1),
+    (1, 16, 1, 2049, 6000, 64, 64, 2, 8, 1),     # sixteen heads, above the split range
+    (1, 4, 2, 1100, 20000, 128, 128, 4, 32, 0),  # 128 candidates
+    (3, 3, 1, 800, 3000, 64, 32, 3, 7, 1),
+])
+def test_middle_rows(shape):
+    """With the full workspace the leaf pairs are grouped by key block; without
+    any, as callers of these sizes could have had, the other schedules run."""
+    B, H, Hkv, Nq, N, d, C, g, K, causal = shape
+    x = inputs.random_qkv(B, H, Hkv, Nq, N, d, "bf16", seed=52)
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, g, K, causal, "bf16")
+    q, k = dev(x["q"], "bf16"), dev(x["k"], "bf16")
+    pyr = pisa.build_pyramid(p, k)
+    idx, sc = pisa.select(p, q, k, pyr, with_score=True)
+    idx2 = torch.empty_like(idx)
+    small = torch.empty(_small_ws(p), dtype=torch.uint8, device="cuda")
+    if B * Hkv * Nq > 2048:
+        pisa.pisa_select(p, q, k, pyr, idx2)
+    else:
+        pisa.pisa_select(p, q, k, pyr, idx2, None, small, small.numel())
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(4), np.linspace(0, Nq - 1, 12).astype(int), np.arange(Nq - 4, Nq)]))
+    for got, score in ((idx, sc), (idx2, None)):
+        got = got.cpu().numpy()
+        check_selection_valid(got, N, Nq, C, K, bool(causal))
+        check_selection_rows(x["q"], x["k"], C, g, K, bool(causal), got[:, :, rows], rows,
+                             gpu_score=None if score is None else score.cpu().numpy()[:, :, rows])
