@@ -126,7 +126,10 @@ int pisa_pyramid_layout(const pisa_problem* p, int64_t* level_row_offset, int64_
 size_t pisa_pyramid_bytes(const pisa_problem* p);
 
 /* Workspace bytes each call needs (0 is a valid answer); 0 also for invalid
- * problems, which the call itself then rejects. */
+ * problems, which the call itself then rejects.  pisa_select
+ * also takes less where the problem has a slower schedule that fits: the
+ * automatic choice below 4096 rows x KV heads, and PISA_SCHEDULE_SPLIT without
+ * its node scores. */
 size_t pisa_select_workspace_bytes(const pisa_problem* p);
 size_t pisa_bsa_workspace_bytes(const pisa_problem* p);
 size_t pisa_attn_workspace_bytes(const pisa_problem* p);
