@@ -530,11 +530,11 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
         const int node = cand[ci];
         int keep = 1;
         if (!fz.is(node)) {
-          const float sc = score[ci];
+          const uint32_t sc = desc_bits(score[ci]);
           int rank = 0;
           for (int cj = 0; cj < nA; ++cj) {
             const int o = cand[cj];
-            rank += (!fz.is(o) && ranks_before(score[cj], o, sc, node)) ? 1 : 0;
+            rank += (!fz.is(o) && word_before(desc_bits(score[cj]), o, sc, node)) ? 1 : 0;
           }
           keep = rank < keepn;
         }
@@ -2267,8 +2267,9 @@ __global__ __launch_bounds__(256) void final_topk_kernel(TopkArgs a, const int32
       const int node = nodes[i];
       int kp = 1;
       if (ranked && !forced(node)) {
+        const uint32_t own = desc_bits(us[i]);
         int rank = 0;
-        for (int j = 0; j < n; ++j) rank += (!forced(nodes[j]) && ranks_before(us[j], nodes[j], us[i], node)) ? 1 : 0;
+        for (int j = 0; j < n; ++j) rank += (!forced(nodes[j]) && word_before(desc_bits(us[j]), nodes[j], own, node)) ? 1 : 0;
         kp = rank < keepn;
       }
       keep[i] = kp;

@@ -22,6 +22,15 @@ __device__ __forceinline__ float desc_bits_inv(uint32_t d) {
   return __uint_as_float(d ^ (~m & 0x7FFFFFFFu));
 }
 
+// Does (word a, index ia) rank before (word b, index ib)?  On desc_bits words
+// this is a total order, NaN included: of n candidates with distinct indices
+// exactly k have fewer than k others before them.  Comparing the floats
+// themselves, every NaN would rank first, and a list that counts on at most K
+// survivors would be overrun.
+__device__ __forceinline__ bool word_before(uint32_t a, int ia, uint32_t b, int ib) {
+  return a < b || (a == b && ia < ib);
+}
+
 // The lanes of a wavefront whose entry e (= lane & 31 for the 32-lane
 // sorts) keeps the smaller of itself and its partner in the bitonic step
 // (K2, J), as a lane mask known at compile time.

@@ -1,0 +1,79 @@
+"""Selection over keys that hold NaN or infinities: every row still selects
+min(K, eligible) distinct blocks, the forced ones among them, and rows that see
+none of those keys select what they would without them (float64 oracle)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_31093_amd import inputs
+from tests.helpers import check_selection_rows, check_selection_valid, dev
+
+pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    from paper_2609_31093_amd import pisa
+else:
+    pisa = None
+
+SPLIT, FUSED, TWO = 3, 2, 1
+
+
+def poison(k, C, first, what):
+    """Every other block from block `first` on: NaN of either sign in every
+    value ("nan", "-nan"), or an infinity in one dimension ("inf": scores of
+    +inf or -inf by the query's sign, NaN where they meet)."""
+    k = k.clone()
+    blocks = torch.arange(first, -(-k.shape[2] // C), 2)
+    rows = (blocks[:, None] * C + torch.arange(C)).flatten().cuda()
+    rows = rows[rows < k.shape[2]]
+    if what == "inf":
+        k[:, :, rows, 3] = float("inf")
+    else:
+        k[:, :, rows] = float("nan")
+        if what == "-nan":
+            bits = k.view(torch.int16 if k.dtype == torch.bfloat16 else torch.int32)
+            bits[:, :, rows] |= torch.iinfo(bits.dtype).min
+    return k
+
+
+def check(B, H, Hkv, Nq, N, d, C, g, K, causal, dtype, schedule, score, what, workspace=None):
+    x = inputs.random_qkv(B, H, Hkv, Nq, N, d, dtype, seed=61)
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, g, K, causal, dtype, schedule=schedule, score=score)
+    q, clean = dev(x["q"], dtype), dev(x["k"], dtype)
+    M1 = -(-N // C)
+    first = M1 // 3
+    k = poison(clean, C, first, what)
+    nb = pisa.pisa_select_workspace_bytes(p) if workspace is None else workspace(p)
+    ws = torch.empty(max(nb, 1), dtype=torch.uint8, device="cuda")
+    idx = torch.empty((B, Hkv, Nq, K), dtype=torch.int32, device="cuda")
+    pisa.pisa_select(p, q, k, pisa.build_pyramid(p, k), idx, None, ws if nb else None, nb)
+    torch.cuda.synchronize()
+    idx = idx.cpu().numpy()
+    check_selection_valid(idx, N, Nq, C, K, bool(causal))
+    before = min(Nq, first * C - (N - Nq))  # rows that see none of the poisoned blocks
+    if causal and before > 0:
+        rows = np.unique(np.linspace(0, before - 1, 12).astype(int))
+        check_selection_rows(x["q"], x["k"], C, g, K, True, idx[:, :, rows], rows,
+                             score=("lse", "mean", "mean_var")[score])
+
+
+def split_floor(p):
+    """The split schedule's workspace without node scores: its candidates, counts and scores."""
+    rows, gK = p.B * p.Hkv * p.Nq, p.fanout * p.K
+    up = lambda n: (n + 255) // 256 * 256
+    return 2 * up(rows * gK * 4) + up(rows * 4)
+
+
+@pytest.mark.parametrize("what", ["nan", "-nan", "inf"])
+@pytest.mark.parametrize("shape", [
+    # ranked by counting the candidates that come before one
+    (1, 2, 1, 40, 16000, 128, 64, 2, 48, 1, "bf16", SPLIT, 0, split_floor),  # 96 candidates, a workgroup per row
+    (1, 2, 1, 40, 16000, 64, 32, 4, 32, 0, "f32", SPLIT, 1, split_floor),    # no forced blocks
+    (1, 1, 1, 300, 9001, 64, 32, 2, 16, 1, "bf16", FUSED, 1, None),          # up to the raw keys
+    (1, 1, 1, 2100, 21000, 64, 32, 4, 50, 1, "bf16", FUSED, 0, None),        # 200 candidates, a wavefront per row
+    (1, 1, 1, 2100, 21000, 64, 32, 4, 50, 1, "bf16", TWO, 0, None),          # ... and in the final Top-K
+    (1, 4, 1, 2100, 21000, 128, 64, 4, 32, 1, "bf16", 0, 0, None),           # the automatic schedule
+])
+def test_counting_rank(shape, what):
+    *problem, workspace = shape
+    check(*problem, what, workspace)
