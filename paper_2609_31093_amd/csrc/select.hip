@@ -343,7 +343,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
   int* L = lds_i + team * lds_words;
   int* cand = L;
   int* cand2 = L + gK;
-  float* score = reinterpret_cast<float*>(L + 2 * gK);
+  uint32_t* word = reinterpret_cast<uint32_t*>(L + 2 * gK);  // rank_word of each candidate of a ranked level
   int* flag = L + 3 * gK;
   int* misc = L + 4 * gK;
   // Per-candidate strides padded by one word so that lanes owning
@@ -442,7 +442,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
         for (int ci = tid; ci < nA; ci += TEAM) {
           const int node = cand[ci];
           float u = 0.f;
-          if (!fz.is(node)) {
+          const bool f = fz.is(node);
+          if (!f) {
             const int nch = min(g, Mb - node * g);
             const bool has_self = !__builtin_isnan(zself[ci * SS]);
             for (int hh = 0; hh < G; ++hh) {
@@ -455,7 +456,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
               u += reduce_logits(a.score_kind, zc, nch, G);
             }
           }
-          score[ci] = u;
+          word[ci] = rank_word(true, f, u);
         }
       } else if constexpr (FUSED) {
         // Leaf level: exact LSE over each candidate block's raw keys.
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
         for (int ci = wave_in_team; ci < nA; ci += NW) {
           const int node = cand[ci];
           if (fz.is(node)) {
-            if (lane == 0) score[ci] = 0.f;
+            if (lane == 0) word[ci] = rank_word(true, true, 0.f);
             continue;
           }
           const int r0 = node * geo.C;
@@ -494,51 +495,35 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
               u += acc_value(a.score_kind, st[hh]);
             }
           }
-          if (lane == 0) score[ci] = u;
+          if (lane == 0) word[ci] = rank_word(true, false, u);
         }
       }
       team_sync<TEAM>();
-      // Rank the non-forced candidates; keep forced + the best K - |F|.
-      const int keepn = a.K - fz.count();
+      // Keep the K that rank first: the forced ones, then score descending,
+      // ties by candidate index (candidates are ascending node ids).
       bool sorted = false;
       if constexpr (TEAM == 64) {
-        if (nA <= 128) {  // one wavefront, two candidates per lane: a bitonic rank sort
-          // Forced candidates sort first (key word 0), then score descending,
-          // ties by candidate index (candidates are ascending node ids), then
-          // the empty slots.
+        if (nA <= 128) {  // one wavefront, two candidates per lane: a bitonic rank sort, empty slots last
           uint32_t hi[2], lo[2];
-          int nforced = 0;
 #pragma unroll
           for (int s2 = 0; s2 < 2; ++s2) {
             const int ci = lane + 64 * s2;
-            const bool v = ci < nA;
-            const bool f = v && fz.is(cand[ci]);
-            hi[s2] = !v ? 0xFFFFFFFFu : (f ? 0u : desc_bits(score[ci]));
+            hi[s2] = ci < nA ? word[ci] : 0xFFFFFFFFu;
             lo[s2] = static_cast<uint32_t>(ci);
-            nforced += __popcll(__ballot(f));
           }
           sort128(hi, lo, lane);
 #pragma unroll
           for (int s2 = 0; s2 < 2; ++s2) {
-            const int r = lane + 64 * s2;  // rank among all candidates
-            if (static_cast<int>(lo[s2]) < nA) flag[lo[s2]] = (r < nforced || r - nforced < keepn) ? 1 : 0;
+            if (static_cast<int>(lo[s2]) < nA) flag[lo[s2]] = lane + 64 * s2 < a.K ? 1 : 0;
           }
           sorted = true;
         }
       }
       for (int ci = tid; !sorted && ci < nA; ci += TEAM) {
-        const int node = cand[ci];
-        int keep = 1;
-        if (!fz.is(node)) {
-          const uint32_t sc = desc_bits(score[ci]);
-          int rank = 0;
-          for (int cj = 0; cj < nA; ++cj) {
-            const int o = cand[cj];
-            rank += (!fz.is(o) && word_before(desc_bits(score[cj]), o, sc, node)) ? 1 : 0;
-          }
-          keep = rank < keepn;
-        }
-        flag[ci] = keep;
+        const uint32_t mine = word[ci];
+        int rank = 0;
+        for (int cj = 0; cj < nA; ++cj) rank += word_before(word[cj], cj, mine, ci) ? 1 : 0;
+        flag[ci] = rank < a.K ? 1 : 0;
       }
     } else {
       for (int ci = tid; ci < nA; ci += TEAM) flag[ci] = 1;
@@ -599,7 +584,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
         const int node = cand[ci];
         a.idx[orow * a.K + pos] = node;
         if (a.score) {
-          a.score[orow * a.K + pos] = (ranked && !f1.is(node)) ? score[ci] * kLn2 : INFINITY;
+          a.score[orow * a.K + pos] = (ranked && !f1.is(node)) ? desc_bits_inv(word[ci]) * kLn2 : INFINITY;
         }
         ++pos;
       }
@@ -2217,7 +2202,7 @@ __global__ __launch_bounds__(256) void final_topk_kernel(TopkArgs a, const int32
                                                          const float* __restrict__ u1,
                                                          int32_t* __restrict__ idx, float* __restrict__ score) {
   __shared__ int s_node[4][kMaxCand];
-  __shared__ float s_u[4][kMaxCand];
+  __shared__ uint32_t s_word[4][kMaxCand];
   __shared__ int s_keep[4][kMaxCand];
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
@@ -2230,49 +2215,39 @@ __global__ __launch_bounds__(256) void final_topk_kernel(TopkArgs a, const int32
   const int32_t* cand = a1 + rg * a.gK;
   const float* uu = u1 + rg * a.gK;
   int* nodes = s_node[wave];
-  float* us = s_u[wave];
+  uint32_t* words = s_word[wave];
   int* keep = s_keep[wave];
   auto forced = [&](int node) { return a.causal && (node == 0 || node == c || node == c - 1); };
   const bool ranked = n > a.K;
-  int nF = 0;
-  if (a.causal) nF = 1 + (c != 0) + (c - 1 > 0);
   for (int i = lane; i < n; i += 64) {
+    const bool f = forced(cand[i]);
     nodes[i] = cand[i];
-    us[i] = (ranked && !forced(cand[i])) ? uu[i] : 0.f;
+    words[i] = rank_word(true, f, (ranked && !f) ? uu[i] : 0.f);
   }
   wave_sync();
-  const int keepn = a.K - nF;
   if (ranked && n <= 128) {
-    // Up to 128 candidates: the 128-entry register sort, forced candidates
-    // keyed below every score, ties by candidate index (ascending nodes).
+    // Up to 128 candidates: the 128-entry register sort (forced first, then
+    // score descending, ties by candidate index, empty slots last).
     uint32_t khi[2], klo[2];
-    int nforced = 0;
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
       const int ci = lane + 64 * s2;
-      const bool v = ci < n;
-      const bool f = v && forced(nodes[ci]);
-      khi[s2] = !v ? 0xFFFFFFFFu : (f ? 0u : desc_bits(us[ci]));
+      khi[s2] = ci < n ? words[ci] : 0xFFFFFFFFu;
       klo[s2] = static_cast<uint32_t>(ci);
-      nforced += __popcll(__ballot(f));
     }
     sort128(khi, klo, lane);
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-      const int rk = lane + 64 * s2;
-      if (static_cast<int>(klo[s2]) < n) keep[klo[s2]] = (rk < nforced || rk - nforced < keepn) ? 1 : 0;
+      if (static_cast<int>(klo[s2]) < n) keep[klo[s2]] = lane + 64 * s2 < a.K ? 1 : 0;
     }
   } else {
     for (int i = lane; i < n; i += 64) {
-      const int node = nodes[i];
-      int kp = 1;
-      if (ranked && !forced(node)) {
-        const uint32_t own = desc_bits(us[i]);
-        int rank = 0;
-        for (int j = 0; j < n; ++j) rank += (!forced(nodes[j]) && word_before(desc_bits(us[j]), nodes[j], own, node)) ? 1 : 0;
-        kp = rank < keepn;
+      int rank = 0;
+      if (ranked) {
+        const uint32_t mine = words[i];
+        for (int j = 0; j < n; ++j) rank += word_before(words[j], j, mine, i) ? 1 : 0;
       }
-      keep[i] = kp;
+      keep[i] = rank < a.K ? 1 : 0;
     }
   }
   wave_sync();
@@ -2292,7 +2267,7 @@ __global__ __launch_bounds__(256) void final_topk_kernel(TopkArgs a, const int32
   for (int i = i0; i < i1; ++i) {
     if (keep[i]) {
       idx[rg * a.K + pos] = nodes[i];
-      if (score) score[rg * a.K + pos] = (ranked && !forced(nodes[i])) ? us[i] * kLn2 : INFINITY;
+      if (score) score[rg * a.K + pos] = (ranked && !forced(nodes[i])) ? desc_bits_inv(words[i]) * kLn2 : INFINITY;
       ++pos;
     }
   }

@@ -22,6 +22,12 @@ __device__ __forceinline__ float desc_bits_inv(uint32_t d) {
   return __uint_as_float(d ^ (~m & 0x7FFFFFFFu));
 }
 
+// The order word of a candidate: forced ones before every score, whatever the
+// scores are (+inf and NaN among them), empty slots last.
+__device__ __forceinline__ uint32_t rank_word(bool valid, bool forced, float score) {
+  return !valid ? 0xFFFFFFFFu : (forced ? 0u : max(desc_bits(score), 1u));
+}
+
 // Does (word a, index ia) rank before (word b, index ib)?  On desc_bits words
 // this is a total order, NaN included: of n candidates with distinct indices
 // exactly k have fewer than k others before them.  Comparing the floats
