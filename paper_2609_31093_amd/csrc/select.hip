@@ -610,19 +610,22 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a, int lds_words) {
 // a compact load list (a candidate whose own logit is known loads one child
 // fewer, see select_kernel), the lane groups of each half (4, 8 or 16 lanes
 // per dot) compute the listed dots, each lane turns its children's logits
-// into its LSE score, and a 32-lane bitonic sort on (score desc, node asc) with forced nodes keyed
-// +inf ranks the half: the first K survive.  Survivors expand through an LDS
+// into its LSE score, and a 32-lane bitonic sort on (forced, score desc, node
+// asc) ranks the half: the first K survive.  Survivors expand through an LDS
 // staging list.  The leaf candidate set is sorted ascending before it is
 // stored.
 // ----------------------------------------------------------------------------
 
-// The best 16 of each wavefront half (key desc, pack asc) in its lanes 0-15,
-// in no particular order, when only that set matters: the network's last
-// merge stops after its first step (each 16-lane run is sorted, in opposite
+// Pack of an empty slot, after every candidate's.
+__device__ __forceinline__ uint32_t empty_pack(int lane) { return 0x7FFFFFC0u | static_cast<uint32_t>(lane); }
+__device__ __forceinline__ bool empty_slot(uint32_t pack) { return pack >= 0x7FFFFFC0u; }
+
+// The first 16 of each wavefront half by (hi, lo) in its lanes 0-15, in no
+// particular order, when only that set matters: the network's last merge
+// stops after its first step (each 16-lane run is sorted, in opposite
 // directions, and lane i keeps the better of i and i ^ 16); `full` finishes
-// the sort (rank order in every lane), as sort32.
-__device__ __forceinline__ void sort32_top16(float& key, int& pack, int hl, bool full) {
-  uint32_t hi = desc_bits(key), lo = static_cast<uint32_t>(pack);
+// the sort (rank order in every lane), as sort32_words.
+__device__ __forceinline__ void sort32_top16(uint32_t& hi, uint32_t& lo, int hl, bool full) {
   sort32_step<2, 1>(hi, lo, hl);
   sort32_step<4, 2>(hi, lo, hl);
   sort32_step<4, 1>(hi, lo, hl);
@@ -640,8 +643,6 @@ __device__ __forceinline__ void sort32_top16(float& key, int& pack, int hl, bool
     sort32_step<32, 2>(hi, lo, hl);
     sort32_step<32, 1>(hi, lo, hl);
   }
-  key = desc_bits_inv(hi);
-  pack = static_cast<int>(lo);
 }
 
 // Inclusive prefix sum over the 32 lanes of a wavefront half.
@@ -797,11 +798,10 @@ __global__ __launch_bounds__(kMfmaSelRows * 64) void stage1_mfma_kernel(SelArgs 
       if (nA <= 32) {  // one 32-lane sort (the upper half sorts nothing of use)
         const bool v = lane < nA;
         const bool f = v && fz.is(cand[lane]);
-        float key = !v ? -INFINITY : (f ? INFINITY : score[lane]);
-        int pack = lane;
+        uint32_t hi = rank_word(v, f, score[lane]), lo = static_cast<uint32_t>(lane);
         const int nforced = __popcll(__ballot(f));
-        sort32(key, pack, lane & 31);
-        if (lane < nA) flag[pack] = (lane < nforced || lane - nforced < keepn) ? 1 : 0;
+        sort32_words(hi, lo, lane & 31);
+        if (lane < nA) flag[lo] = (lane < nforced || lane - nforced < keepn) ? 1 : 0;
       } else {  // two candidates per lane: the 128-entry sort (forced keyed below every score)
         uint32_t khi[2], klo[2];
         int nforced = 0;
@@ -1071,11 +1071,10 @@ __global__ __launch_bounds__(kUnionWaves * 64) void stage1_union_kernel(SelArgs 
           const bool v = lane < nAr[r];
           const int node = v ? cand[r * 128 + lane] : 0;
           const bool f = v && fz.is(node);
-          float key = !v ? -INFINITY : (f ? INFINITY : score_of(r, node));
-          int pack = lane;
+          uint32_t hi = rank_word(v, f, v && !f ? score_of(r, node) : 0.f), lo = static_cast<uint32_t>(lane);
           const int nforced = __popcll(__ballot(f));
-          sort32(key, pack, lane & 31);
-          if (lane < nAr[r]) flag[r * 128 + pack] = (lane < nforced || lane - nforced < keepn) ? 1 : 0;
+          sort32_words(hi, lo, lane & 31);
+          if (lane < nAr[r]) flag[r * 128 + lo] = (lane < nforced || lane - nforced < keepn) ? 1 : 0;
         }
       } else {
         uint32_t khi[R][2], klo[R][2];
@@ -1287,7 +1286,7 @@ __global__ __launch_bounds__(256) void stage1_pair_kernel(SelArgs a, int row_wor
     const bool valid = node >= 0;
     const bool isf = valid && fz.is(node);
     const int nch = valid ? min(g, Mb - node * g) : 0;
-    float key = valid ? INFINITY : -INFINITY;
+    float score = 0.f;
     if (ranked) {
       // 1) compact list of the child rows to load
       const bool has_self = !__builtin_isnan(zs[0]);
@@ -1349,20 +1348,20 @@ __global__ __launch_bounds__(256) void stage1_pair_kernel(SelArgs a, int row_wor
             u += reduce_logits(a.score_kind, zc, nch, G);
           }
         }
-        key = u;
+        score = u;
       }
     }
-    // 4) rank: the first K in (key desc, node asc) order survive
+    // 4) rank: the first K in (forced, score desc, node asc) order survive
     int knode = node, korig = hl;
     bool kept = active && valid;
     if (__ballot(ranked) != 0) {
-      int pack = valid ? (node << 6) | hl : 0x7FFFFFC0 | hl;
-      float skey = key;
-      sort32(skey, pack, hl);
+      uint32_t hi = rank_word(valid, isf, score);
+      uint32_t pack = valid ? static_cast<uint32_t>((node << 6) | hl) : empty_pack(hl);
+      sort32_words(hi, pack, hl);
       if (ranked) {
-        kept = hl < K && skey != -INFINITY;
-        knode = pack >> 6;
-        korig = pack & 63;
+        kept = hl < K && !empty_slot(pack);
+        knode = static_cast<int>(pack >> 6);
+        korig = static_cast<int>(pack & 63);
       }
     }
     const bool known = ranked && kept && !fz.is(knode);
@@ -1415,9 +1414,9 @@ __global__ __launch_bounds__(256) void stage1_pair_kernel(SelArgs a, int row_wor
 //     dot, child 1 derived from the node's own logit (a summary is the mean of
 //     its two children, so z1 = 2 z - z0), except on the row's first ranked
 //     level, where own logits are unknown and child 1 is a dot as well.
-//   * Rank: key = score (scored), +inf (forced, or every valid slot of an
-//     unranked level), -inf (empty slot); a 32-lane bitonic sort puts the
-//     survivors in lanes 0 .. min(K, #valid) - 1.
+//   * Rank: rank_word (forced slots and every valid slot of an unranked level
+//     first, empty slots last); a 32-lane bitonic sort puts the survivors in
+//     lanes 0 .. min(K, #valid) - 1.
 //   * Expand: slot s of the next level is child s & 1 of survivor s >> 1; its
 //     node and its own logit come from the survivor's lanes by lane permutes.
 // ----------------------------------------------------------------------------
@@ -1521,9 +1520,9 @@ __device__ __forceinline__ float pair_score(float z0, float z1) {
 }
 
 // One level of the fan-out-2 walk for the two rows of a wavefront: rank the
-// slots (first K in (key desc, node asc) order survive; scored slots keyed by
-// their summed score, forced slots and every slot of an unranked level +inf,
-// empty slots -inf) and expand the survivors: slot s of the next level is
+// slots (first K in (word, node) order survive, word = rank_word: forced slots
+// and every slot of an unranked level, then scored slots by their summed score,
+// then empty slots) and expand the survivors: slot s of the next level is
 // child s & 1 of survivor s >> 1, its own logits taken from the survivor's
 // child logits.  A half idle on this level (lev above its start) stays idle.
 template <int GMAX, int KIND>
@@ -1536,33 +1535,26 @@ __device__ __forceinline__ void g2_rank_expand(const Geo& geo, int lev, int c, i
   const int nvalid = __builtin_popcount(static_cast<uint32_t>(__ballot(valid) >> hbase));
   const bool ranked = nvalid > K;  // more candidates than the budget
   const Forced fz = forced_at(geo, lev, c, causal);
-  float key = -INFINITY;
-  if (valid) {
-    if (ranked && !fz.is(node)) {
-      float u = 0.f;
+  float u = 0.f;
 #pragma unroll
-      for (int hh = 0; hh < GMAX; ++hh) {
-        const float sc = pair_score<KIND>(z0[hh], z1[hh]);
-        u += hh < G ? sc : 0.f;
-      }
-      key = u;
-    } else {
-      key = INFINITY;
-    }
+  for (int hh = 0; hh < GMAX; ++hh) {
+    const float sc = pair_score<KIND>(z0[hh], z1[hh]);
+    u += hh < G ? sc : 0.f;
   }
-  int pack = valid ? (node << 6) | hl : 0x7FFFFFC0 | hl;
+  uint32_t word = rank_word(valid, !ranked || fz.is(node), u);
+  uint32_t pack = valid ? static_cast<uint32_t>((node << 6) | hl) : empty_pack(hl);
   // With K = 16 only the set of the best 16 matters (a survivor's place
   // among the next level's slots does not), so the sort stops early; the
   // survivors then sit in lanes 0-15 in any order, empty slots among them.
-  sort32_top16(key, pack, hl, K != 16);
+  sort32_top16(word, pack, hl, K != 16);
   const int nkept = K == 16 ? 16 : min(K, nvalid);
 
   const int r = hl >> 1;
-  const int pr = __shfl(pack, hbase | r);
+  const int pr = __shfl(static_cast<int>(pack), hbase | r);
   const int korig = pr & 63;
   const int rmax = causal ? min(anc_at(geo, c, lb), Mb - 1) : Mb - 1;
   const int cn = 2 * (pr >> 6) + (hl & 1);
-  const bool cvalid = r < nkept && pr < 0x7FFFFFC0 && cn <= rmax;
+  const bool cvalid = r < nkept && !empty_slot(static_cast<uint32_t>(pr)) && cn <= rmax;
 #pragma unroll
   for (int hh = 0; hh < GMAX; ++hh) {
     const float a0 = __shfl(z0[hh], hbase | korig);
@@ -1864,11 +1856,10 @@ __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
     // The first K in (score desc, block asc) order, forced blocks first, back
     // in ascending order.
     __shared__ int s_rank[NWAVE][64];
-    float key = -INFINITY;
-    if (valid) key = ranked && !isf ? us : INFINITY;
-    const float own = key;
-    int pack = valid ? (leaf << 6) | hl : 0x7FFFFFC0 | hl;
-    sort32(key, pack, hl);
+    const bool scored = ranked && !isf;
+    uint32_t word = rank_word(valid, !scored, us);
+    uint32_t pack = valid ? static_cast<uint32_t>((leaf << 6) | hl) : empty_pack(hl);
+    sort32_words(word, pack, hl);
     s_rank[wave][hbase + (pack & 63)] = hl;
     wave_sync();
     const bool kept = valid && s_rank[wave][lane] < K;
@@ -1878,7 +1869,7 @@ __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
       const int64_t orow = (static_cast<int64_t>(bh) * a.Nq + row) * K;
       if (kept) {
         a.idx[orow + incl - 1] = leaf;
-        if (a.score) a.score[orow + incl - 1] = own == INFINITY ? INFINITY : own * kLn2;
+        if (a.score) a.score[orow + incl - 1] = scored ? us * kLn2 : INFINITY;
       }
       if (hl >= total && hl < K) {
         a.idx[orow + hl] = -1;
@@ -1890,8 +1881,8 @@ __global__ __launch_bounds__(NWAVE * 64) void stage1_g2_kernel(SelArgs a) {
 
 // Final Top-K for g*K <= 32: a row per 32-lane half of a wavefront (RP such
 // pairs of rows per wavefront), one candidate per lane (the candidates
-// arrive in ascending block order).  sort32 ranks them
-// (forced and unranked rows keyed +inf); the rank of each lane's own
+// arrive in ascending block order).  A 32-lane sort ranks them
+// (forced ones and unranked rows first); the rank of each lane's own
 // candidate comes back through LDS and the kept ones are compacted in their
 // original, ascending order with a prefix sum.
 template <int RP>
@@ -1922,24 +1913,23 @@ __global__ __launch_bounds__(256) void final_topk_pair_kernel(TopkArgsP a, const
     node_raw[p] = a1[rgc * a.gK + slot];
     u_raw[p] = u1[rgc * a.gK + slot];
   }
-  float key[RP], own[RP];
-  int pack[RP], node[RP];
-  bool valid[RP];
+  uint32_t word[RP], pack[RP];
+  int node[RP];
+  bool valid[RP], scored[RP];
 #pragma unroll
   for (int p = 0; p < RP; ++p) {
     const bool ranked = n[p] > a.K;
     valid[p] = hl < n[p];
     node[p] = valid[p] ? node_raw[p] : -1;
     const bool isf = a.causal && valid[p] && (node[p] == 0 || node[p] == c[p] || node[p] == c[p] - 1);
-    key[p] = -INFINITY;
-    if (valid[p]) key[p] = (ranked && !isf) ? u_raw[p] : INFINITY;
-    own[p] = key[p];
-    pack[p] = valid[p] ? (node[p] << 6) | hl : 0x7FFFFFC0 | hl;
+    scored[p] = ranked && !isf;
+    word[p] = rank_word(valid[p], !scored[p], u_raw[p]);
+    pack[p] = valid[p] ? static_cast<uint32_t>((node[p] << 6) | hl) : empty_pack(hl);
   }
   // lane q of the sorted half holds rank q (with K = 16 only the best 16 are
   // separated from the rest); send it back to the source lane
 #pragma unroll
-  for (int p = 0; p < RP; ++p) sort32_top16(key[p], pack[p], hl, a.K != 16);
+  for (int p = 0; p < RP; ++p) sort32_top16(word[p], pack[p], hl, a.K != 16);
 #pragma unroll
   for (int p = 0; p < RP; ++p) s_rank[wave][p][(lane & 32) + (pack[p] & 63)] = hl;
   wave_sync();
@@ -1951,7 +1941,7 @@ __global__ __launch_bounds__(256) void final_topk_pair_kernel(TopkArgsP a, const
       const int total = half_total(incl, lane);
       if (kept) {
         idx[rg[p] * a.K + incl - 1] = node[p];
-        if (score) score[rg[p] * a.K + incl - 1] = (own[p] == INFINITY) ? INFINITY : own[p] * kLn2;
+        if (score) score[rg[p] * a.K + incl - 1] = scored[p] ? u_raw[p] * kLn2 : INFINITY;
       }
       if (hl >= total && hl < a.K) {
         idx[rg[p] * a.K + hl] = -1;
@@ -2286,7 +2276,7 @@ __global__ __launch_bounds__(256) void final_topk_kernel(TopkArgs a, const int32
 // eligible nodes), all 256 threads fetch every child row of the level at
 // once (16 lanes per row) and leave the logits in LDS, and wavefront 0 holds
 // one candidate per lane, forms the LSE scores, ranks them with a 64-lane
-// bitonic sort (forced nodes keyed +inf), keeps the first K and expands them
+// bitonic sort (forced nodes first), keeps the first K and expands them
 // to their eligible children through a lane scan.
 // ----------------------------------------------------------------------------
 template <int K2, int J>
@@ -2307,10 +2297,8 @@ __device__ __forceinline__ void sort64_step(uint32_t& hi, uint32_t& lo, int lane
   lo = take ? olo : lo;
 }
 
-// Bitonic sort of the 64 lanes of a wavefront into rank order (key desc,
-// pack asc); packs are non-negative.
-__device__ __forceinline__ void sort64(float& key, int& pack, int lane) {
-  uint32_t hi = desc_bits(key), lo = static_cast<uint32_t>(pack);
+// Bitonic sort of the 64 lanes of a wavefront by (hi, lo), ascending.
+__device__ __forceinline__ void sort64_words(uint32_t& hi, uint32_t& lo, int lane) {
   sort64_step<2, 1>(hi, lo, lane);
   sort64_step<4, 2>(hi, lo, lane);
   sort64_step<4, 1>(hi, lo, lane);
@@ -2332,6 +2320,12 @@ __device__ __forceinline__ void sort64(float& key, int& pack, int lane) {
   sort64_step<64, 4>(hi, lo, lane);
   sort64_step<64, 2>(hi, lo, lane);
   sort64_step<64, 1>(hi, lo, lane);
+}
+
+// The same into rank order (key desc, pack asc); packs are non-negative.
+__device__ __forceinline__ void sort64(float& key, int& pack, int lane) {
+  uint32_t hi = desc_bits(key), lo = static_cast<uint32_t>(pack);
+  sort64_words(hi, lo, lane);
   key = desc_bits_inv(hi);
   pack = static_cast<int>(lo);
 }
@@ -2441,27 +2435,28 @@ __global__ __launch_bounds__(256) void stage1_row_kernel(SelArgs a) {
       const bool valid = node >= 0;
       const bool isf = valid && fz.is(node);
       const bool ranked = nA > K;
-      float key = valid ? INFINITY : -INFINITY;
+      float score = 0.f;
       if (ranked && valid && !isf) {
         const int nch = min(g, Mb - node * g);
         float u = 0.f;
         for (int hh = 0; hh < G; ++hh) {
           u += reduce_logits(a.score_kind, s_z + lane * g * G + hh, nch, G);
         }
-        key = u;
+        score = u;
       }
       int knode = node;
       bool kept = valid;
       if (ranked) {
-        int pack = valid ? node : 0x7FFFFFC0 | lane;
+        uint32_t word = rank_word(valid, isf, score);
+        uint32_t pack = valid ? static_cast<uint32_t>(node) : empty_pack(lane);
         // at most 32 candidates (g*K <= 32) sit in lanes 0-31: a 32-lane
         // sort (with K = 16 only the best 16 separated from the rest) ranks them
         if (a.gK <= 32)
-          sort32_top16(key, pack, lane & 31, K != 16);
+          sort32_top16(word, pack, lane & 31, K != 16);
         else
-          sort64(key, pack, lane);
-        kept = lane < K && key != -INFINITY;
-        knode = pack;
+          sort64_words(word, pack, lane);
+        kept = lane < K && !empty_slot(pack);
+        knode = static_cast<int>(pack);
       }
       // 3) expand the kept nodes to their eligible children
       const int rmax = a.causal ? min(anc_at(geo, c, lev - 1), Mb - 1) : Mb - 1;
@@ -2589,18 +2584,18 @@ __device__ __forceinline__ int walk_levels(const SelArgs& a, int c, int lane, co
   for (int lev = start; lev >= 2; --lev) {
     const Forced fz = forced_at(geo, lev, c, a.causal);
     const bool valid = node >= 0, ranked = nA > K;
-    float key = valid ? INFINITY : -INFINITY;
-    if (ranked && valid && !fz.is(node)) key = sc[base + node];
     int knode = node;
     bool kept = valid;
     if (ranked) {
-      int pack = valid ? node : 0x7FFFFFC0 | lane;
+      const bool f = valid && fz.is(node);
+      uint32_t word = rank_word(valid, f, valid && !f ? sc[base + node] : 0.f);
+      uint32_t pack = valid ? static_cast<uint32_t>(node) : empty_pack(lane);
       if (a.gK <= 32)
-        sort32_top16(key, pack, lane & 31, K != 16);
+        sort32_top16(word, pack, lane & 31, K != 16);
       else
-        sort64(key, pack, lane);
-      kept = lane < K && key != -INFINITY;
-      knode = pack;
+        sort64_words(word, pack, lane);
+      kept = lane < K && !empty_slot(pack);
+      knode = static_cast<int>(pack);
     }
     const int rmax = a.causal ? min(anc_at(geo, c, lev - 1), geo.M[lev - 1] - 1) : geo.M[lev - 1] - 1;
     const int c0 = knode * g;

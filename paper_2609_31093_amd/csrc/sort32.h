@@ -68,10 +68,8 @@ __device__ __forceinline__ void sort32_step(uint32_t& hi, uint32_t& lo, int hl) 
   lo = take ? olo : lo;
 }
 
-// Bitonic sort of the 32 lanes of each wavefront half into rank order
-// (key desc, pack asc); packs are non-negative.
-__device__ __forceinline__ void sort32(float& key, int& pack, int hl) {
-  uint32_t hi = desc_bits(key), lo = static_cast<uint32_t>(pack);
+// Bitonic sort of the 32 lanes of each wavefront half by (hi, lo), ascending.
+__device__ __forceinline__ void sort32_words(uint32_t& hi, uint32_t& lo, int hl) {
   sort32_step<2, 1>(hi, lo, hl);
   sort32_step<4, 2>(hi, lo, hl);
   sort32_step<4, 1>(hi, lo, hl);
@@ -87,6 +85,12 @@ __device__ __forceinline__ void sort32(float& key, int& pack, int hl) {
   sort32_step<32, 4>(hi, lo, hl);
   sort32_step<32, 2>(hi, lo, hl);
   sort32_step<32, 1>(hi, lo, hl);
+}
+
+// The same into rank order (key desc, pack asc); packs are non-negative.
+__device__ __forceinline__ void sort32(float& key, int& pack, int hl) {
+  uint32_t hi = desc_bits(key), lo = static_cast<uint32_t>(pack);
+  sort32_words(hi, lo, hl);
   key = desc_bits_inv(hi);
   pack = static_cast<int>(lo);
 }

@@ -77,3 +77,26 @@ def split_floor(p):
 def test_counting_rank(shape, what):
     *problem, workspace = shape
     check(*problem, what, workspace)
+
+
+@pytest.mark.parametrize("what", ["nan", "-nan", "inf"])
+@pytest.mark.parametrize("shape", [
+    # ranked by sorts across 32 or 64 lanes
+    (1, 1, 1, 2101, 9001, 64, 64, 2, 4, 1, "f32", FUSED, 0, None),          # row pairs up to the raw keys
+    (1, 1, 1, 2101, 9001, 128, 32, 2, 16, 1, "f32", FUSED, 1, None),        # ... with the sort that stops early
+    (1, 4, 1, 2060, 9001, 128, 64, 2, 7, 1, "bf16", FUSED, 0, None),
+    (1, 1, 1, 2060, 9001, 64, 32, 2, 9, 0, "f32", FUSED, 2, None),          # no forced blocks
+    (1, 1, 1, 5000, 9001, 128, 64, 2, 16, 1, "bf16", TWO, 0, None),         # row pairs, then the final Top-K
+    (1, 4, 1, 4500, 9001, 64, 64, 2, 5, 1, "bf16", TWO, 1, None),
+    (1, 2, 1, 300, 9001, 64, 32, 3, 7, 1, "bf16", TWO, 0, None),            # fan-out 3
+    (1, 8, 1, 200, 9001, 128, 64, 2, 16, 1, "bf16", TWO, 0, None),          # matrix cores, up to 32 candidates
+    (1, 2, 1, 300, 9001, 64, 32, 2, 20, 1, "bf16", TWO, 1, None),           # ... over the union of four rows
+    (1, 2, 1, 5, 20000, 128, 32, 2, 16, 1, "bf16", SPLIT, 0, split_floor),  # few rows, level by level
+    (1, 2, 1, 5, 20000, 128, 32, 2, 30, 1, "f32", SPLIT, 1, split_floor),
+    (1, 2, 1, 5, 20000, 128, 32, 2, 16, 1, "bf16", SPLIT, 0, None),         # ... from node scores
+    (1, 2, 1, 5, 20000, 128, 32, 2, 30, 1, "f32", SPLIT, 1, None),
+    (1, 2, 1, 5, 60000, 64, 32, 4, 30, 1, "bf16", SPLIT, 0, None),          # two candidates per lane
+])
+def test_forced_blocks_first(shape, what):
+    *problem, workspace = shape
+    check(*problem, what, workspace)
