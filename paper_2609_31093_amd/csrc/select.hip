@@ -1648,7 +1648,8 @@ __device__ __forceinline__ float wave_block_score(const SelArgs& a, const T* __r
         float v = acc[hh][0] + acc[hh][1];
         v += xor32_f<1>(v);
         v += xor32_f<2>(v);
-        z[hh][p] = r < nrows ? v : -INFINITY;
+        // keys past the block: nothing to the LSE; the other reducers count them out below
+        z[hh][p] = KIND != kScoreLse || r < nrows ? v : -INFINITY;
       }
     }
 #pragma unroll
@@ -1661,7 +1662,20 @@ __device__ __forceinline__ float wave_block_score(const SelArgs& a, const T* __r
         for (int p = 0; p < 4; ++p) t[hh] += fast_exp2(z[hh][p] - ref);
         m[hh] = mn;
       } else {
-        acc_merge(KIND, st[hh], acc_of<4>(KIND, z[hh]));
+        float n = 0.f, sum = 0.f, m2 = 0.f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const bool ok = base + p * KPP + key0 < nrows;
+          n += ok ? 1.f : 0.f;
+          sum += ok ? z[hh][p] : 0.f;
+        }
+        const float mean = n > 0.f ? sum / n : 0.f;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const float dv = z[hh][p] - mean;
+          m2 += base + p * KPP + key0 < nrows ? dv * dv : 0.f;
+        }
+        acc_merge(KIND, st[hh], ScoreAcc{n, mean, m2});
       }
     }
   }
@@ -1675,7 +1689,7 @@ __device__ __forceinline__ float wave_block_score(const SelArgs& a, const T* __r
         float mx = sel_max(dpp_f<0x128>(m[hh]), m[hh]);  // row_ror:8, row_ror:4
         mx = sel_max(dpp_f<0x124>(mx), mx);
         mx = sel_max(sel_max(at(mx, 0), at(mx, 16)), sel_max(at(mx, 32), at(mx, 48)));
-        float sm = t[hh] * fast_exp2(m[hh] - mx);
+        float sm = t[hh] * fast_exp2(m[hh] - (mx == -INFINITY ? 0.f : mx));  // no finite logit: a score of -inf
         sm += dpp_f<0x128>(sm);
         sm += dpp_f<0x124>(sm);
         u += mx + fast_log2((at(sm, 0) + at(sm, 16)) + (at(sm, 32) + at(sm, 48)));

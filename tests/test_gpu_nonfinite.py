@@ -100,3 +100,41 @@ def test_counting_rank(shape, what):
 def test_forced_blocks_first(shape, what):
     *problem, workspace = shape
     check(*problem, what, workspace)
+
+
+@pytest.mark.parametrize("dtype,H,Hkv", [("f32", 3, 3), ("bf16", 12, 3)])
+def test_blocks_of_minus_infinity_rank_last(dtype, H, Hkv):
+    """Blocks whose every logit is -inf (keys of -inf in a dimension where the
+    queries are positive) score -inf and are kept only where nothing else is
+    left; only the leaf level is ranked here."""
+    B, d, C, K = 1, 64, 32, 16
+    N = Nq = 1024  # 32 blocks under 16 nodes
+    x = inputs.random_qkv(B, H, Hkv, Nq, N, d, dtype, seed=62)
+    x["q"][..., 3] = np.abs(x["q"][..., 3]) + 0.25
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, 2, K, 1, dtype, schedule=FUSED)
+    q, k = dev(x["q"], dtype), dev(x["k"], dtype)
+    clean = k.double()
+    bad = torch.arange(1, N // C, 4)
+    rows = (bad[:, None] * C + torch.arange(C)).flatten().cuda()
+    k[:, :, rows, 3] = float("-inf")
+    idx, sc = pisa.select(p, q, k, pisa.build_pyramid(p, k), with_score=True)
+    torch.cuda.synchronize()
+    check_selection_valid(idx.cpu().numpy(), N, Nq, C, K, True)
+    z = torch.matmul(q.double().view(B, Hkv, H // Hkv, Nq, d), clean.transpose(2, 3)[:, :, None]) / d ** 0.5
+    want = z.view(B, Hkv, H // Hkv, Nq, N // C, C).logsumexp(-1).sum(2)  # [B, Hkv, Nq, blocks]
+    want[..., bad.cuda()] = float("-inf")
+    kept = idx.clamp(min=0).long()
+    scored = torch.isfinite(sc) | torch.isneginf(sc) & (idx >= 0)
+    ref = want.gather(-1, kept)
+    assert bool(scored.any())
+    ok = (sc.double() - ref).abs() < 1e-3
+    assert bool((ok | (torch.isneginf(ref) & torch.isneginf(sc)))[scored].all())
+    # no finite block is left out for one of -inf
+    t = torch.arange(Nq, device="cuda")
+    eligible = torch.arange(N // C, device="cuda") <= (t // C)[:, None]
+    taken = (idx[..., None] == torch.arange(N // C, device="cuda")).any(-2)
+    left_finite = (eligible & torch.isfinite(want) & ~taken).any(-1)
+    forced = torch.stack([torch.zeros_like(t), (t // C - 1).clamp(min=0), t // C], -1)
+    is_forced = (kept[..., None] == forced[None, None, :, None]).any(-1)
+    took_bad = (torch.isneginf(ref) & (idx >= 0) & ~is_forced).any(-1)
+    assert bool(left_finite.any()) and not bool((left_finite & took_bad).any())
