@@ -174,16 +174,36 @@ constexpr int kMaxClusterBins = 16384;
 // spreads each row's leaf candidates over workgroups of their own.
 constexpr int64_t kSplitMaxRows = 2048;
 
-// Rows from which it groups the leaf pairs by key block: key-block reuse pays
-// once many queries share the key blocks (Sec. 3.3).  With up to four heads
-// per KV head from 2048 query rows of single heads on (one head: 8 x 256 rows
-// over 60000 keys 183 -> 145 us; four: 4 x 128 rows over 30000 keys 108 -> 94,
-// 2 x 256 rows with g*K = 128 over 200000 keys 446 -> 244; one head with 8 x
-// 128 rows: 114 against 120), with more above the split schedule's range (16
-// heads, 2 x 512 rows: 340 against 343 us; 2 x 1025 rows, where the fused
-// schedule served: 1230 -> 580).
-bool two_stage_pays(const pisa::Shape& s, int64_t rows) {
-  return s.G <= 4 ? rows * s.G >= kSplitMaxRows : rows > kSplitMaxRows;
+// Fewer rows than kTwoStageRows: does grouping the leaf pairs by key block
+// pay?  Only rows of one (batch, KV head) share its key blocks, and the
+// grouping costs 30 us and more, the longer the more rows a head has (few
+// workgroups count and place them), against leaf scores that the split
+// schedule (up to 2048 rows) or the fused one spreads over the device.
+//   * A row scores the min(g*K, M1) candidates of the leaf level when there are
+//     more than K of them: M1 >= 2 K (g*K = 128 over 32 blocks, 2 x 1500 rows of 4
+//     heads: 17 us fused, 199 grouped).
+//   * Four rows to a key block, or one per 16 keys where that is more: decode,
+//     however many sequences, is not grouped (512 KV heads x 1 row of 4 heads,
+//     131072 keys: 127 us split, 1508 grouped; 16 KV heads x 64 rows, 32768
+//     keys, 4 rows to a block: 155 and 122; 32 x 32 rows, 2 to a block: 159
+//     and 170).
+//   * Work to save: keys x dims x heads of one row's scored candidates, over
+//     the KV heads.  Up to four heads, g*K = 32, 64-key blocks, d = 128, over
+//     8192 keys: 2 KV heads x 1024 rows of 4 heads 259 and 223 us, 8 x 256 rows
+//     260 and 100; 4 x 512 rows of one head 129 and 97, 2 x 1024 rows 128 and
+//     150.  d = 64, g*K = 16, 4000 rows of one head on one KV head: 33 and 100.
+//   * More than four heads, where the other schedules have no kernel that
+//     shares loads among them: above the split schedule's range (16 heads,
+//     2 x 1025 rows, g*K = 16, 30000 keys: 1158 and 529); not for lists of a
+//     few candidates (g*K = 8: 570 and 650).
+// Over 7298 shapes (1 to 300 KV heads, 8 to 256 candidates, 32- to 256-key
+// blocks) the choice is more than 4% slower than the other one at 5.
+bool two_stage_pays(const pisa::Shape& s, const pisa::Geo& g, int64_t rows) {
+  const int64_t M1 = g.M[1], scored = std::min<int64_t>(s.gK(), M1) - s.K;
+  if (M1 < 2 * s.K || 16LL * s.Nq * s.gK() < std::max(64, s.C) * M1) return false;
+  if (s.G > 4) return rows > kSplitMaxRows && scored >= 8;
+  if (rows * s.G < kSplitMaxRows || scored < 16 || (s.BH() < 2 && rows <= kSplitMaxRows)) return false;
+  return static_cast<int64_t>(s.BH()) * s.G * s.C * s.D * scored >= 1 << 20;
 }
 
 // From this many rows the automatic schedule insists on the two-stage
@@ -194,7 +214,7 @@ constexpr int64_t kTwoStageRows = 4096;
 int pick_schedule(const pisa_problem* p, const pisa::Shape& s, const pisa::Geo& g, bool small_ws = false) {
   if (p->schedule != PISA_SCHEDULE_AUTO) return p->schedule;
   const int64_t rows = static_cast<int64_t>(s.Nq) * s.BH();
-  if (s.bf16 && g.M[1] <= kMaxClusterBins && (rows >= kTwoStageRows || (!small_ws && two_stage_pays(s, rows))))
+  if (s.bf16 && g.M[1] <= kMaxClusterBins && (rows >= kTwoStageRows || (!small_ws && two_stage_pays(s, g, rows))))
     return PISA_SCHEDULE_TWO_STAGE;
   return rows <= kSplitMaxRows ? PISA_SCHEDULE_SPLIT : PISA_SCHEDULE_FUSED;
 }
