@@ -1535,13 +1535,16 @@ __device__ __forceinline__ void g2_rank_expand(const Geo& geo, int lev, int c, i
   const int nvalid = __builtin_popcount(static_cast<uint32_t>(__ballot(valid) >> hbase));
   const bool ranked = nvalid > K;  // more candidates than the budget
   const Forced fz = forced_at(geo, lev, c, causal);
-  float u = 0.f;
+  uint32_t word = valid ? 0u : 0xFFFFFFFFu;
+  if (valid && ranked && !fz.is(node)) {
+    float u = 0.f;
 #pragma unroll
-  for (int hh = 0; hh < GMAX; ++hh) {
-    const float sc = pair_score<KIND>(z0[hh], z1[hh]);
-    u += hh < G ? sc : 0.f;
+    for (int hh = 0; hh < GMAX; ++hh) {
+      const float sc = pair_score<KIND>(z0[hh], z1[hh]);
+      u += hh < G ? sc : 0.f;
+    }
+    word = rank_word(true, false, u);
   }
-  uint32_t word = rank_word(valid, !ranked || fz.is(node), u);
   uint32_t pack = valid ? static_cast<uint32_t>((node << 6) | hl) : empty_pack(hl);
   // With K = 16 only the set of the best 16 matters (a survivor's place
   // among the next level's slots does not), so the sort stops early; the
@@ -1689,7 +1692,7 @@ __device__ __forceinline__ float wave_block_score(const SelArgs& a, const T* __r
         float mx = sel_max(dpp_f<0x128>(m[hh]), m[hh]);  // row_ror:8, row_ror:4
         mx = sel_max(dpp_f<0x124>(mx), mx);
         mx = sel_max(sel_max(at(mx, 0), at(mx, 16)), sel_max(at(mx, 32), at(mx, 48)));
-        float sm = t[hh] * fast_exp2(m[hh] - (mx == -INFINITY ? 0.f : mx));  // no finite logit: a score of -inf
+        float sm = t[hh] * fast_exp2(m[hh] - fmaxf(mx, -3.0e38f));  // no finite logit: a score of -inf, not NaN
         sm += dpp_f<0x128>(sm);
         sm += dpp_f<0x124>(sm);
         u += mx + fast_log2((at(sm, 0) + at(sm, 16)) + (at(sm, 32) + at(sm, 48)));
