@@ -9,7 +9,7 @@
  * Conventions shared by every entry point
  * ---------------------------------------
  * - Every buffer pointer is a DEVICE pointer unless stated otherwise and must
- *   be 16-byte aligned.  The caller allocates and owns every buffer,
+ *   be 16-byte aligned (workspaces 256-byte).  The caller allocates and owns every buffer,
  *   including workspaces; the library never allocates device memory, never
  *   synchronises and never creates streams.
  * - Every compute call is asynchronous on `stream` (a hipStream_t; 0 is the
@@ -127,9 +127,9 @@ size_t pisa_pyramid_bytes(const pisa_problem* p);
 
 /* Workspace bytes each call needs (0 is a valid answer); 0 also for invalid
  * problems, which the call itself then rejects.  pisa_select
- * also takes less where the problem has a slower schedule that fits: the
- * automatic choice below 4096 rows x KV heads, and PISA_SCHEDULE_SPLIT without
- * its node scores. */
+ * also takes less (or none, or a misaligned one as none) where the problem has
+ * a slower schedule that fits: the automatic choice below 4096 rows x KV heads,
+ * and PISA_SCHEDULE_SPLIT without its node scores. */
 size_t pisa_select_workspace_bytes(const pisa_problem* p);
 size_t pisa_bsa_workspace_bytes(const pisa_problem* p);
 size_t pisa_attn_workspace_bytes(const pisa_problem* p);

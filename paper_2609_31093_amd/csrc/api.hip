@@ -152,12 +152,14 @@ int check_ptr(const void* ptr, const char* name, bool nullable = false) {
   return PISA_OK;
 }
 
+bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) == 0; }
+
 int check_ws(void* ws, size_t ws_bytes, size_t need) {
   if (need == 0) return PISA_OK;
   if (ws_bytes < need)
     return fail(PISA_ERR_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, need);
   if (!ws) return fail(PISA_ERR_WORKSPACE, "workspace is NULL, need %zu bytes", need);
-  if ((reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return fail(PISA_ERR_INVALID_ARG, "workspace not 256-byte aligned");
+  if (!aligned256(ws)) return fail(PISA_ERR_INVALID_ARG, "workspace not 256-byte aligned");
   return PISA_OK;
 }
 
@@ -231,7 +233,8 @@ size_t select_ws_min(int sched, const pisa::Shape& s, const pisa::Geo& g) {
   return sched == PISA_SCHEDULE_SPLIT ? pisa::select_split_ws_min(s) : select_ws(sched, s, g);
 }
 
-// Settles the schedule for a workspace of ws_bytes, and how its stage 1 runs.
+// Settles the schedule for a workspace with ws_bytes of use (none where it is
+// NULL or misaligned), and how its stage 1 runs.
 int schedule_for_ws(const pisa_problem* p, pisa::Shape* s, const pisa::Geo& g, int sched, size_t ws_bytes) {
   if (ws_bytes < select_ws_min(sched, *s, g)) sched = pick_schedule(p, *s, g, true);
   s->plain_stage1 = p->schedule == PISA_SCHEDULE_AUTO && static_cast<int64_t>(s->Nq) * s->BH() < kTwoStageRows;
@@ -306,7 +309,7 @@ int static_scratch(void** out) {
     g_scratch_ptr[dev] = ptr;
   });
   if (g_scratch_err[dev] != hipSuccess) return device_status(g_scratch_err[dev], "hipGetSymbolAddress(scratch)");
-  if ((reinterpret_cast<uintptr_t>(g_scratch_ptr[dev]) & 255u) != 0)
+  if (!aligned256(g_scratch_ptr[dev]))
     return fail(PISA_ERR_DEVICE, "static scratch is not 256-byte aligned");
   *out = g_scratch_ptr[dev];
   return PISA_OK;
@@ -461,7 +464,7 @@ int pisa_select(const pisa_problem* p, const void* q, const void* k, const float
   pisa::Geo g{};
   int sched = 0;
   PISA_TRY(check_select(p, q, k, pyramid, block_idx, block_score, &s, &g, &sched));
-  sched = schedule_for_ws(p, &s, g, sched, ws ? ws_bytes : 0);
+  sched = schedule_for_ws(p, &s, g, sched, ws && aligned256(ws) ? ws_bytes : 0);
   PISA_TRY(check_ws(ws, ws_bytes, select_ws_min(sched, s, g)));
   return run_select(s, g, sched, q, k, pyramid, block_idx, block_score, ws, ws_bytes, static_cast<hipStream_t>(stream),
                     "pisa_select");

@@ -39,3 +39,27 @@ def test_grouped_rows(shape):
     check_selection_valid(idx, N, Nq, C, K, bool(causal))
     rows = np.unique(np.concatenate([np.arange(2), np.linspace(0, Nq - 1, 6).astype(int), np.arange(Nq - 2, Nq)]))
     check_selection_rows(x["q"], x["k"], C, g, K, bool(causal), idx[:, :, rows], rows, gpu_score=sc[:, :, rows])
+
+
+def test_workspaces_of_no_use():
+    """Rows that the fused schedule serves without a workspace take any: none,
+    a small one, or one that is not aligned, whose bytes stay as they are.  The
+    split schedule, which needs one, refuses it."""
+    B, H, Hkv, Nq, N, d, C, g, K = 1, 16, 4, 600, 9001, 64, 64, 2, 16
+    x = inputs.random_qkv(B, H, Hkv, Nq, N, d, "bf16", seed=72)
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, g, K, 1, "bf16")
+    q, k = dev(x["q"], "bf16"), dev(x["k"], "bf16")
+    pyr = pisa.build_pyramid(p, k)
+    need = pisa.pisa_select_workspace_bytes(p)
+    assert need > 0
+    want = torch.empty((B, Hkv, Nq, K), dtype=torch.int32, device="cuda")
+    pisa.pisa_select(p, q, k, pyr, want)
+    ws = torch.full((need + 256,), 0x5A, dtype=torch.uint8, device="cuda")
+    idx = torch.empty_like(want)
+    pisa.pisa_select(p, q, k, pyr, idx, None, ws[16:], need)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, want) and bool((ws == 0x5A).all())
+    few = pisa.make_problem(B, H, Hkv, 300, N, d, C, g, K, 1, "bf16")
+    with pytest.raises(pisa.PisaError) as e:
+        pisa.pisa_select(few, q[:, :, :300].contiguous(), k, pyr, idx, None, ws[16:], need)
+    assert e.value.status == pisa.PISA_ERR_INVALID_ARG
