@@ -638,8 +638,9 @@ __device__ __forceinline__ void bsa_list_tile(const BsaArgs& a, const uint16_t* 
   }
 }
 
-// redo: only the tiles that the scan kernels marked; each workgroup looks at
-// 256 tiles' marks at a time.
+// redo: only the tiles that the scan kernels marked.  Workgroup w owns tiles
+// w, w + gridDim.x, ... and looks at 256 of their marks at a time; neighbouring
+// tiles, which mostly are marked together, go to different workgroups.
 template <int D, int KP, int GM>
 __global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint16_t* __restrict__ phi,
                                                           const uint16_t* __restrict__ plo, int BH, bool redo) {
@@ -650,14 +651,13 @@ __global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint1
   }
   __shared__ int todo[256], ntodo;
   const int64_t ntiles = static_cast<int64_t>(ntx) * BH;
-  const int64_t per = (ntiles + gridDim.x - 1) / gridDim.x;
-  const int64_t end = min(ntiles, per * (blockIdx.x + 1));
-  for (int64_t base = per * blockIdx.x; base < end; base += 256) {
+  const int64_t step = gridDim.x;
+  for (int64_t base = blockIdx.x; base < ntiles; base += 256 * step) {
     __syncthreads();
     if (threadIdx.x == 0) ntodo = 0;
     __syncthreads();
-    const int64_t i = base + threadIdx.x;
-    if (i < end) {
+    const int64_t i = base + threadIdx.x * step;
+    if (i < ntiles) {
       const int64_t row = (i / ntx) * a.Nq + (i % ntx) * 64;
       const bool more = (i % ntx) * 64 + 32 < a.Nq;
       if (a.idx[row * a.K] == kBsaRedo || (more && a.idx[(row + 32) * a.K] == kBsaRedo))
@@ -665,7 +665,7 @@ __global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint1
     }
     __syncthreads();
     for (int n = 0; n < ntodo; ++n) {
-      const int64_t t = base + todo[n];
+      const int64_t t = base + todo[n] * step;
       bsa_list_tile<D, KP, GM>(a, phi, plo, static_cast<int>(t % ntx), static_cast<int>(t / ntx));
       __syncthreads();
     }

@@ -15,7 +15,11 @@
 //
 // Rows that this does not decide (a list that runs over, NaN) are marked
 // kBsaRedo in the output and ranked by the exact list kernel afterwards, a
-// launch that otherwise reads one mark per 32 rows (6 us).
+// launch that otherwise reads one mark per 32 rows (6 us).  That costs more than
+// the list kernel alone only where nearly every tile is marked: 32 heads on 8 KV
+// heads, 131072 rows, d = 128, K = 16: 15.9 -> 6.0 ms without marks, 15.7 -> 8.3
+// with the tiles of one KV head marked (all of its keys equal), 10.7 -> 17.3 with
+// all of them.
 //
 // Measured (MI355X, the list kernel alone -> scan kernels and that launch):
 // one head, 8 x 131072 rows, d = 128, K = 16: 5.04 -> 1.19 ms; 16 heads,
@@ -618,9 +622,10 @@ __global__ __launch_bounds__(256, 2) void bsa_group_kernel(BsaArgs a, int BH, co
     }
   }
   // A class whose third block reaches T may hold more that do: its wavefront
-  // scores its tiles again for those.
+  // scores its tiles again for those, unless the list ran over already.
+  __syncthreads();
   uint32_t more = 0;
-  if (ranked && T > -INFINITY) {
+  if (ranked && T > -INFINITY && cnt[col] <= CAP) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) more |= s3[r] >= T ? 1u << r : 0u;
   }

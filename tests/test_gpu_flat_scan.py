@@ -89,3 +89,29 @@ def test_one_class_holds_the_best(H):
         x["k"][:, :, j * C:(j + 1) * C] = inputs.round_to_bf16((3 + 0.25 * n) * u.astype(np.float32))
     idx = _run(x, B, H, Hkv, Nq, N, d, C, K, 1)
     _check(x, idx, N, Nq, C, K, 1, np.arange(Nq))
+
+
+@pytest.mark.parametrize("B,H,Hkv,Nq,K,equal", [
+    (8, 4, 1, 4100, 8, "all"),     # 520 tiles of 64 rows, each marked: two to some workgroups of the exact kernel
+    (8, 2, 1, 8300, 16, "all"),    # 1040 of them
+    (8, 4, 1, 4100, 8, "some"),    # the tiles of every other batch entry
+    (8, 1, 1, 4100, 8, "all"),     # one head: the scans decide ties
+])
+def test_marked_tiles(B, H, Hkv, Nq, K, equal):
+    """Keys that are all equal: every block scores the same and the smaller
+    ones are kept, beside the forced ones."""
+    N, d, C = Nq, 64, 64
+    gen = torch.Generator(device="cuda").manual_seed(34)
+    q, k = (torch.randn((B, h, N, d), generator=gen, device="cuda").bfloat16() for h in (H, Hkv))
+    marked = slice(None) if equal == "all" else slice(1, None, 2)
+    k[marked] = 0.5
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, 2, K, 1, "bf16")
+    idx = pisa.select_flat_bsa(p, q, pisa.build_pyramid(p, k))
+    c = (torch.arange(Nq, device="cuda") // C)[:, None]
+    j = torch.arange(K, device="cuda")[None]
+    want = torch.where(c < K, torch.where(j <= c, j, -1), torch.where(j < K - 2, j, c - (K - 1) + j))
+    assert torch.equal(idx[marked], want.int().expand_as(idx[marked]))
+    if equal == "some":
+        rows = np.array([0, 63, 64, 2000, Nq - 1])
+        x = {"q": q[:1].float().cpu().numpy(), "k": k[:1].float().cpu().numpy()}
+        check_flat_bsa_rows(x["q"], x["k"], C, K, True, idx[:1, :, rows].cpu().numpy(), rows)
