@@ -631,8 +631,8 @@ __device__ __forceinline__ void bsa_list_tile(const BsaArgs& a, const uint16_t* 
     int* sq = sel + wave * 32;
     if (lane < a.K) sq[lane] = x;
     wave_sync();
-    int rank = 0;
-    for (int y = 0; y < a.K; ++y) rank += sq[y] < x ? 1 : 0;
+    int rank = 0;  // (places that nothing ranks for, with NaN scores, stay apart)
+    for (int y = 0; y < a.K; ++y) rank += sq[y] < x || (sq[y] == x && y < lane) ? 1 : 0;
     if (lane < a.K) out[rank] = x == 0x7fffffff ? -1 : x;
     wave_sync();
   }

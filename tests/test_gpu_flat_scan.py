@@ -115,3 +115,34 @@ def test_marked_tiles(B, H, Hkv, Nq, K, equal):
         rows = np.array([0, 63, 64, 2000, Nq - 1])
         x = {"q": q[:1].float().cpu().numpy(), "k": k[:1].float().cpu().numpy()}
         check_flat_bsa_rows(x["q"], x["k"], C, K, True, idx[:1, :, rows].cpu().numpy(), rows)
+
+
+@pytest.mark.parametrize("H", [1, 4])
+@pytest.mark.parametrize("K", [16, 24])
+def test_nan(H, K):
+    """A block of NaN keys and a few NaN queries: rows that see neither select
+    what they would without them, the other rows what can be ranked (with one
+    head: every other block) and their forced blocks, padded with -1."""
+    B, Hkv, Nq, N, d, C = 1, 1, 200, 8192, 64, 32
+    x = inputs.random_qkv(B, H, Hkv, Nq, N, d, "bf16", seed=35)
+    j = 253  # of 256; rows 0-103 end before it, and it is no row's forced block from row 168 on
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, 2, K, 1, "bf16")
+    q, k = dev(x["q"], "bf16"), dev(x["k"], "bf16")
+    clean = pisa.select_flat_bsa(p, q, pisa.build_pyramid(p, k)).cpu().numpy()[0, 0]
+    k[:, :, j * C:(j + 1) * C] = float("nan")
+    q[:, :, 40:200:50] = float("nan")
+    idx = pisa.select_flat_bsa(p, q, pisa.build_pyramid(p, k)).cpu().numpy()[0, 0]
+    nan_q = np.isin(np.arange(Nq), np.arange(40, 200, 50))
+    for r in range(Nq):
+        c = (N - Nq + r) // C
+        row = idx[r]
+        got = row[row >= 0]
+        assert np.all(np.diff(got) > 0) and {0, c - 1, c} <= set(got) and np.all(row[len(got):] == -1)
+        if nan_q[r]:
+            assert list(got) == [0, c - 1, c]
+        elif c < j:
+            assert np.array_equal(row, clean[r])
+        elif c > j + 1 and H == 1:
+            assert len(got) == K and j not in got and set(clean[r]) - {j} <= set(got)
+    rows = np.array([0, 1, 39, 41, 88, 91, 103])
+    check_flat_bsa_rows(x["q"], x["k"], C, K, True, idx[None, None, rows], rows)
