@@ -646,7 +646,7 @@ __global__ __launch_bounds__(256, 2) void bsa_mfma_kernel(BsaArgs a, const uint1
                                                           const uint16_t* __restrict__ plo, int BH, bool redo) {
   const int ntx = (a.Nq + 63) / 64;
   if (!redo) {
-    bsa_list_tile<D, KP, GM>(a, phi, plo, blockIdx.x % ntx, blockIdx.x / ntx);
+    bsa_list_tile<D, KP, GM>(a, phi, plo, blockIdx.x, blockIdx.y);
     return;
   }
   __shared__ int todo[256], ntodo;
@@ -716,8 +716,9 @@ hipError_t launch_flat_bsa(const Shape& s, const Geo& geo, const void* q, const 
     }
     // After a scan: the marked tiles only, on a grid that a device holds.
     ProfScope ps("bsa_mfma", st);
-    const int64_t ntiles = static_cast<int64_t>((s.Nq + 63) / 64) * s.BH();
-    const unsigned grid = static_cast<unsigned>(scan ? std::min<int64_t>(ntiles, 512) : ntiles);
+    const int ntx = (s.Nq + 63) / 64;
+    const dim3 grid = scan ? dim3(static_cast<unsigned>(std::min<int64_t>(static_cast<int64_t>(ntx) * s.BH(), 512)))
+                           : dim3(ntx, s.BH());
     const int KP = s.K <= 16 ? 16 : 32;
     // staged chunk (hi + lo rows), the score tile and the lists; the pass-1
     // merge reuses the chunk area

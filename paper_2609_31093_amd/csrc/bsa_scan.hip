@@ -31,6 +31,7 @@
 #include "bsa.h"
 #include "common.h"
 #include "kernels.h"
+#include "launch_grid.h"
 #include "sort32.h"
 #include "sortnet.h"
 
@@ -69,6 +70,9 @@ __device__ __forceinline__ bool rankable(const BsaArgs& a, const RowBlocks& r, i
 // Block of accumulator register r in tile `ch`: v_mfma_f32_32x32x16 leaves row
 // 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile in register r.
 __device__ __forceinline__ int tile_block(int ch, int half, int r) { return ch * 32 + 8 * (r >> 2) + 4 * half + (r & 3); }
+
+// The workgroup's row tile in a head_grid launch.
+__device__ __forceinline__ int grid_tile() { return static_cast<int>(blockIdx.z * gridDim.y + blockIdx.y); }
 
 // Writes one row's ascending selection: the best blocks (keepn of them, any
 // order, in id[0..16)) and the forced ones.
@@ -119,7 +123,7 @@ __device__ __forceinline__ void emit_row16(const BsaArgs& a, int32_t* __restrict
 constexpr int kScanCap = 28;  // collected blocks per query: two workgroups fit a CU
 
 template <int D, int QT>
-__global__ __launch_bounds__(256, 2) void bsa_scan_kernel(BsaArgs a, int BH, const uint16_t* __restrict__ phi,
+__global__ __launch_bounds__(256, 2) void bsa_scan_kernel(BsaArgs a, const uint16_t* __restrict__ phi,
                                                           const uint16_t* __restrict__ plo) {
   constexpr int KS = D / 16;
   constexpr int ROW = D + 8;
@@ -133,8 +137,10 @@ __global__ __launch_bounds__(256, 2) void bsa_scan_kernel(BsaArgs a, int BH, con
   const int col = lane & 31, half = lane >> 5;
   // longest rows first; a head's tiles on every BH-th workgroup
   const int ntx = (a.Nq + NQ - 1) / NQ;
-  const int bh = blockIdx.x % BH;
-  const int wg0 = (ntx - 1 - static_cast<int>(blockIdx.x / BH)) * NQ;
+  const int tx = grid_tile();
+  if (tx >= ntx) return;
+  const int bh = blockIdx.x;
+  const int wg0 = (ntx - 1 - tx) * NQ;
   const int b = bh / a.Hkv, h = bh - b * a.Hkv;
   const int row0 = wg0 + wave * 32 * QT;
   const int first = a.N - a.Nq;
@@ -382,7 +388,7 @@ size_t group_lds(int G, int D) {
 }
 
 template <int D, int GM, int KP>
-__global__ __launch_bounds__(256, 2) void bsa_group_kernel(BsaArgs a, int BH, const uint16_t* __restrict__ phi,
+__global__ __launch_bounds__(256, 2) void bsa_group_kernel(BsaArgs a, const uint16_t* __restrict__ phi,
                                                            const uint16_t* __restrict__ plo) {
   constexpr int KS = D / 16;
   constexpr int CH = D / 8;  // 16-byte chunks of a row
@@ -399,8 +405,10 @@ __global__ __launch_bounds__(256, 2) void bsa_group_kernel(BsaArgs a, int BH, co
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int ntx = (a.Nq + 31) / 32;
-  const int bh = blockIdx.x % BH;
-  const int row0 = (ntx - 1 - static_cast<int>(blockIdx.x / BH)) * 32;
+  const int tx = grid_tile();
+  if (tx >= ntx) return;
+  const int bh = blockIdx.x;
+  const int row0 = (ntx - 1 - tx) * 32;
   const int b = bh / a.Hkv, h = bh - b * a.Hkv;
   const int first = a.N - a.Nq;
   const int c_lo = (first + row0) / a.C;
@@ -699,33 +707,38 @@ bool bsa_scan_path(int G, int K) {
   return G == 1 ? K <= 16 : K <= 32;
 }
 
+static dim3 tile_grid(int tiles, int BH) {
+  const HeadGrid g = head_grid(tiles, BH);
+  return dim3(g.x, g.y, g.z);
+}
+
 hipError_t launch_bsa_scan(const BsaArgs& a, int BH, int D, const uint16_t* phi, const uint16_t* plo, hipStream_t st) {
   if (a.G == 1) {
     // 256 rows per workgroup once that gives every CU its two workgroups, 128
     // below (8 heads: 25 vs 36 us at 4097 rows, 63 either way at 16384, 153
     // vs 136 at 32768)
     const bool wide = static_cast<int64_t>((a.Nq + 255) / 256) * BH >= 512;
-    const unsigned grid = static_cast<unsigned>(((a.Nq + (wide ? 255 : 127)) / (wide ? 256 : 128)) * BH);
+    const dim3 grid = tile_grid((a.Nq + (wide ? 255 : 127)) / (wide ? 256 : 128), BH);
     if (D == 128) {
       if (wide)
-        bsa_scan_kernel<128, 2><<<grid, 256, 0, st>>>(a, BH, phi, plo);
+        bsa_scan_kernel<128, 2><<<grid, 256, 0, st>>>(a, phi, plo);
       else
-        bsa_scan_kernel<128, 1><<<grid, 256, 0, st>>>(a, BH, phi, plo);
+        bsa_scan_kernel<128, 1><<<grid, 256, 0, st>>>(a, phi, plo);
     } else {
       if (wide)
-        bsa_scan_kernel<64, 2><<<grid, 256, 0, st>>>(a, BH, phi, plo);
+        bsa_scan_kernel<64, 2><<<grid, 256, 0, st>>>(a, phi, plo);
       else
-        bsa_scan_kernel<64, 1><<<grid, 256, 0, st>>>(a, BH, phi, plo);
+        bsa_scan_kernel<64, 1><<<grid, 256, 0, st>>>(a, phi, plo);
     }
     return hipGetLastError();
   }
   const int KP = a.K <= 16 ? 16 : 32;
   const size_t lds = KP == 16 ? group_lds<16>(a.G, D) : group_lds<32>(a.G, D);
-  const unsigned grid = static_cast<unsigned>(((a.Nq + 31) / 32) * BH);
+  const dim3 grid = tile_grid((a.Nq + 31) / 32, BH);
   auto go = [&](auto kern) {
     if (lds > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-    kern<<<grid, 256, lds, st>>>(a, BH, phi, plo);
+    kern<<<grid, 256, lds, st>>>(a, phi, plo);
   };
   if (D == 128) {
     if (a.G <= 4)
