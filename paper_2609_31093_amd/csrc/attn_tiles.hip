@@ -25,8 +25,11 @@ constexpr int kMergeBatch = 4;  // partials requested together
 // KB: registers per lane and column group for the slots that are read ahead
 // (a column's four lanes hold KB slots each); budgets above 4 KB take the rest
 // in the merge.
+// The two staged blocks of 96 or more keys of 128 values leave room in the LDS
+// for one workgroup per CU, which may then have all of its registers: nothing
+// is spilled.
 template <int D, int CT, int G, int KB>
-__global__ __launch_bounds__(kTileWaves * 64, 2) void attn_tile_kernel(
+__global__ __launch_bounds__(kTileWaves * 64, CT * D > 256 ? 1 : 2) void attn_tile_kernel(
     AttnBlockArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ idx, uint16_t* __restrict__ o, float* __restrict__ lse,
     const uint16_t* __restrict__ part_o, const float* __restrict__ part_lse, int ltiles, int lcount) {
@@ -130,7 +133,12 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void attn_tile_kernel(
         lsv[cg][i] = far(xs[cg][i], cr[cg]) ? part_lse[(pb + 4 * i + grp) * G + hq] : -INFINITY;
       }
       const int32_t* sl = idx + (static_cast<int64_t>(bh) * a.Nq + rowc[cg]) * a.K;
-      for (int s = 4 * KB + grp; s < a.K; s += 4) f |= bits(sl[s]);
+      // (the same trip count in every lane: the compiler has been seen to store
+      // spilled registers after a divergent loop here before it gave the lanes back)
+      for (int s0 = 4 * KB; s0 < a.K; s0 += 4) {
+        const int x = sl[min(s0 + grp, a.K - 1)];  // (the last slot twice does no harm)
+        f |= bits(x);
+      }
       f |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(f), 16));
       f |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(f), 32));
       sel[cg] = vrow[cg] ? f : 0u;
