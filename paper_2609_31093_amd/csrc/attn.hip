@@ -1598,13 +1598,13 @@ static hipError_t launch_block_path(const Shape& s, const Geo& geo, const void* 
     }
     // With several heads per KV head, the row tiles of this chunk that the
     // union kernel did not take go through the row-tile kernel of
-    // attn_tiles.hip: the forced blocks staged once per tile for every head,
+    // attn_tiles.h: the forced blocks staged once per tile for every head,
     // then the far partials merged.
     if (a.tile_order) {
       ProfScope ps("attn_local", st);
-      e = launch_attn_tiles(a, s.BH(), D, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
-                            static_cast<const uint16_t*>(v), idx, static_cast<uint16_t*>(o), lse, part_o, part_lse,
-                            st);
+      e = launch_attn_tiles<D>(a, s.BH(), static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                               static_cast<const uint16_t*>(v), idx, static_cast<uint16_t*>(o), lse, part_o, part_lse,
+                               st);
       if (e != hipSuccess) return e;
     } else if (local) {
       ProfScope ps("attn_local", st);

@@ -1,4 +1,4 @@
-// Shared by the block-centric attention kernels (attn.hip, attn_tiles.hip).
+// Shared by the block-centric attention kernels (attn.hip, attn_tiles.h).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -56,12 +56,13 @@ template <int NCH>
 __device__ __forceinline__ int union_swz(int r) {
   return NCH == 16 ? (r & 15) : ((r >> 1) & 7);
 }
-// The row-tile kernel for the forced blocks of G > 1 rows (attn_tiles.hip):
+// The row-tile kernel for the forced blocks of G > 1 rows (attn_tiles.h):
 // rows [a.row0, a.row0 + a.nrows) that the union kernel did not take.
 constexpr int kTileWaves = 4;  // wavefronts per workgroup
 inline int attn_tile_rows(int G) { return kTileWaves * kUnionGroups * 16 / G; }
-hipError_t launch_attn_tiles(const AttnBlockArgs& a, int BH, int D, const uint16_t* q, const uint16_t* k,
-                             const uint16_t* v, const int32_t* idx, uint16_t* o, float* lse, const uint16_t* part_o,
+template <int D>
+hipError_t launch_attn_tiles(const AttnBlockArgs& a, int BH, const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                             const int32_t* idx, uint16_t* o, float* lse, const uint16_t* part_o,
                              const float* part_lse, hipStream_t st);
 
 }  // namespace pisa

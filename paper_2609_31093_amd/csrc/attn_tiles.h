@@ -14,6 +14,8 @@
 // blocks, built first, made it eight.  Bound by those waits and the partials'
 // bytes.  32 heads on 2 KV heads, 131072 rows, d = 64, K = 8:
 // 1.58 -> 1.07 ms (1.33 with the partials in natural order, 8-byte loads).
+#pragma once
+
 #include <algorithm>
 
 #include "attn_shared.h"
@@ -23,12 +25,11 @@ namespace pisa {
 constexpr int kMergeBatch = 4;  // partials requested together
 
 // KB: registers per lane and column group for the slots that are read ahead
-// (a column's four lanes hold KB slots each); budgets above 4 KB take the rest
-// in the merge.
+// (a column's four lanes hold KB slots each).  TAIL: budgets above 4 KB, whose
+// further slots are read in the merge; without it nothing of theirs is kept.
 // The two staged blocks of 96 or more keys of 128 values leave room in the LDS
-// for one workgroup per CU, which may then have all of its registers: nothing
-// is spilled.
-template <int D, int CT, int G, int KB>
+// for one workgroup per CU, which may then have all of its registers.
+template <int D, int CT, int G, int KB, bool TAIL>
 __global__ __launch_bounds__(kTileWaves * 64, CT * D > 256 ? 1 : 2) void attn_tile_kernel(
     AttnBlockArgs a, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ idx, uint16_t* __restrict__ o, float* __restrict__ lse,
@@ -132,12 +133,12 @@ __global__ __launch_bounds__(kTileWaves * 64, CT * D > 256 ? 1 : 2) void attn_ti
         f |= bits(xs[cg][i]);
         lsv[cg][i] = far(xs[cg][i], cr[cg]) ? part_lse[(pb + 4 * i + grp) * G + hq] : -INFINITY;
       }
-      const int32_t* sl = idx + (static_cast<int64_t>(bh) * a.Nq + rowc[cg]) * a.K;
-      // (the same trip count in every lane: the compiler has been seen to store
-      // spilled registers after a divergent loop here before it gave the lanes back)
-      for (int s0 = 4 * KB; s0 < a.K; s0 += 4) {
-        const int x = sl[min(s0 + grp, a.K - 1)];  // (the last slot twice does no harm)
-        f |= bits(x);
+      if constexpr (TAIL) {
+        const int32_t* sl = idx + (static_cast<int64_t>(bh) * a.Nq + rowc[cg]) * a.K;
+        for (int s0 = 4 * KB; s0 < a.K; s0 += 4) {
+          const int x = sl[min(s0 + grp, a.K - 1)];  // (the last slot twice does no harm)
+          f |= bits(x);
+        }
       }
       f |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(f), 16));
       f |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(f), 32));
@@ -305,16 +306,18 @@ __global__ __launch_bounds__(kTileWaves * 64, CT * D > 256 ? 1 : 2) void attn_ti
         for (int u = 0; u < kMergeBatch; ++u) ls[u] = __shfl(lsv[cg][i], col | (u << 4));
         merge(4 * i, ls);
       }
-      const int32_t* sl = idx + (static_cast<int64_t>(bh) * a.Nq + rowc[cg]) * a.K;
-      for (int s0 = 4 * KB; s0 < a.K; s0 += kMergeBatch) {  // budgets above 4 KB
-        float ls[kMergeBatch];
+      if constexpr (TAIL) {
+        const int32_t* sl = idx + (static_cast<int64_t>(bh) * a.Nq + rowc[cg]) * a.K;
+        for (int s0 = 4 * KB; s0 < a.K; s0 += kMergeBatch) {  // budgets above 4 KB
+          float ls[kMergeBatch];
 #pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-          const int sx = s0 + u;
-          const int x = sx < a.K ? sl[sx] : -1;
-          ls[u] = far(x, cr[cg]) ? part_lse[(pb + sx) * G + hq] : -INFINITY;
+          for (int u = 0; u < kMergeBatch; ++u) {
+            const int sx = s0 + u;
+            const int x = sx < a.K ? sl[sx] : -1;
+            ls[u] = far(x, cr[cg]) ? part_lse[(pb + sx) * G + hq] : -INFINITY;
+          }
+          merge(s0, ls);
         }
-        merge(s0, ls);
       }
       if (!vrow[cg]) continue;
       // oacc[cg][dt][i] = O[d = dt*16 + 4*grp + i][this column]
@@ -332,8 +335,9 @@ __global__ __launch_bounds__(kTileWaves * 64, CT * D > 256 ? 1 : 2) void attn_ti
   }
 }
 
-hipError_t launch_attn_tiles(const AttnBlockArgs& a, int BH, int D, const uint16_t* q, const uint16_t* k,
-                             const uint16_t* v, const int32_t* idx, uint16_t* o, float* lse, const uint16_t* part_o,
+template <int D>
+hipError_t launch_attn_tiles(const AttnBlockArgs& a, int BH, const uint16_t* q, const uint16_t* k, const uint16_t* v,
+                             const int32_t* idx, uint16_t* o, float* lse, const uint16_t* part_o,
                              const float* part_lse, hipStream_t st) {
   const int T = attn_tile_rows(a.G);
   const int ltiles = (a.row0 + a.nrows + T - 1) / T - a.row0 / T;
@@ -348,28 +352,27 @@ hipError_t launch_attn_tiles(const AttnBlockArgs& a, int BH, int D, const uint16
     const unsigned grid = static_cast<unsigned>(std::min(lcount, per_cu * kDeviceCUs));
     kern<<<grid, kTileWaves * 64, lds, st>>>(a, q, k, v, idx, o, lse, part_o, part_lse, ltiles, lcount);
   };
-#define PISA_TILE_KB(DD, CT, GG) \
+// Budgets from 17 to 32 read all of their slots ahead too (2 heads, 8192 rows,
+// 30000 keys, d = 64, K = 32: 160 -> 148 us for the whole call; 16 heads on 4 KV
+// heads, 4096 rows, d = 128, K = 32: 344 -> 336).
+#define PISA_TILE_KB(CT, GG) \
   do { \
-    if (a.K <= 8) go(attn_tile_kernel<DD, CT, GG, 2>); \
-    else go(attn_tile_kernel<DD, CT, GG, 4>); \
+    if (a.K <= 8) go(attn_tile_kernel<D, CT, GG, 2, false>); \
+    else if (a.K <= 16) go(attn_tile_kernel<D, CT, GG, 4, false>); \
+    else if (a.K <= 32) go(attn_tile_kernel<D, CT, GG, 8, false>); \
+    else go(attn_tile_kernel<D, CT, GG, 8, true>); \
   } while (0)
-#define PISA_TILE_G(DD, CT) \
+#define PISA_TILE_G(CT) \
   do { \
-    if (a.G == 2) PISA_TILE_KB(DD, CT, 2); \
-    else if (a.G == 4) PISA_TILE_KB(DD, CT, 4); \
-    else if (a.G == 8) PISA_TILE_KB(DD, CT, 8); \
-    else PISA_TILE_KB(DD, CT, 16); \
+    if (a.G == 2) PISA_TILE_KB(CT, 2); \
+    else if (a.G == 4) PISA_TILE_KB(CT, 4); \
+    else if (a.G == 8) PISA_TILE_KB(CT, 8); \
+    else PISA_TILE_KB(CT, 16); \
   } while (0)
-#define PISA_TILE_C(DD) \
-  do { \
-    if (a.C == 32) PISA_TILE_G(DD, 1); \
-    else if (a.C == 64) PISA_TILE_G(DD, 2); \
-    else if (a.C == 96) PISA_TILE_G(DD, 3); \
-    else PISA_TILE_G(DD, 4); \
-  } while (0)
-  if (D == 128) PISA_TILE_C(128);
-  else PISA_TILE_C(64);
-#undef PISA_TILE_C
+  if (a.C == 32) PISA_TILE_G(1);
+  else if (a.C == 64) PISA_TILE_G(2);
+  else if (a.C == 96) PISA_TILE_G(3);
+  else PISA_TILE_G(4);
 #undef PISA_TILE_G
 #undef PISA_TILE_KB
   return hipGetLastError();
