@@ -391,12 +391,17 @@ __global__ __launch_bounds__(NW * 64, (CT >= 3 ? 1 : NW == 8 ? 4 : 3)) void attn
       // partial rows go through LDS so that each store writes whole rows
       // (16 lanes x 16 bytes per row, four rows per instruction).
       uint16_t* tb = tbuf + wave * (16 * TBS);
+      // two places a lane, the rest constant offsets (a choice between the
+      // orders per d tile cost 128-key blocks a seventh: 277 -> 317 us at 2 x
+      // 16384 rows of 4 heads, d = 128, K = 16; 275 so)
+      uint16_t* tcol = tb + col * TBS + grp * (a.tile_order ? 8 : 4);
+      const int todd = a.tile_order ? 4 : 16;  // from an even d tile's values to the next one's
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
         uint2 w;
         w.x = pack2_bf16(oacc[dt][0] * inv, oacc[dt][1] * inv);
         w.y = pack2_bf16(oacc[dt][2] * inv, oacc[dt][3] * inv);
-        *reinterpret_cast<uint2*>(tb + col * TBS + (a.tile_order ? (dt >> 1) * 32 + grp * 8 + (dt & 1) * 4 : dt * 16 + 4 * grp)) = w;
+        *reinterpret_cast<uint2*>(tcol + (dt >> 1) * 32 + ((dt & 1) ? todd : 0)) = w;
       }
       if (valid && grp == 0) part_lse[pidx] = l > 0.f ? m + fast_log2(l) : -INFINITY;
       wave_sync();
