@@ -10,6 +10,7 @@
 // natural log.
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "attn_shared.h"
 #include "common.h"
@@ -190,8 +191,18 @@ __global__ __launch_bounds__(256) void attn_rows_kernel(AttnArgs a) {
 constexpr int kAttnChunk = 1024;  // pairs of one selected-block cluster per workgroup (key block staged once)
 constexpr int kAttnBlockWaves = 8;  // wavefronts per workgroup of attn_block16_kernel
 
-template <int D, int CT, int NW>
-__global__ __launch_bounds__(NW * 64, (CT >= 3 ? 1 : NW == 8 ? 4 : 3)) void attn_block16_kernel(AttnBlockArgs a, const uint16_t* __restrict__ q,
+// TILES: the partials' values in the row-tile kernel's order (AttnBlockArgs::
+// tile_order), else in natural order.  Compiled apart: where the order was
+// chosen as a partial is stored, the registers of 128-key blocks went another
+// way (277 -> 317 us at 2 x 16384 rows of 4 heads, d = 128; 331 -> 392 at 8192
+// rows of 16, d = 64).
+// PAIRED: 128-key blocks with d = 64 in 128 registers a lane, so that two
+// workgroups fit a CU.  Faster where a block is mostly staging (54 -> 45 us at
+// 16384 rows of one head; 161 -> 148 for the whole call at 2 x 16384 rows of 2),
+// slower where its products want the loads further ahead (91 -> 106 at 8192 rows of 4).
+template <int D, int CT, int NW, bool TILES, bool PAIRED>
+__global__ __launch_bounds__(NW * 64, (CT >= 3 ? (PAIRED ? 4 : 1) : NW == 8 ? 4 : 3)) void attn_block16_kernel(
+                                                           AttnBlockArgs a, const uint16_t* __restrict__ q,
                                                            const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v,
                                                            const int32_t* __restrict__ offs,
@@ -391,17 +402,13 @@ __global__ __launch_bounds__(NW * 64, (CT >= 3 ? 1 : NW == 8 ? 4 : 3)) void attn
       // partial rows go through LDS so that each store writes whole rows
       // (16 lanes x 16 bytes per row, four rows per instruction).
       uint16_t* tb = tbuf + wave * (16 * TBS);
-      // two places a lane, the rest constant offsets (a choice between the
-      // orders per d tile cost 128-key blocks a seventh: 277 -> 317 us at 2 x
-      // 16384 rows of 4 heads, d = 128, K = 16; 275 so)
-      uint16_t* tcol = tb + col * TBS + grp * (a.tile_order ? 8 : 4);
-      const int todd = a.tile_order ? 4 : 16;  // from an even d tile's values to the next one's
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
         uint2 w;
         w.x = pack2_bf16(oacc[dt][0] * inv, oacc[dt][1] * inv);
         w.y = pack2_bf16(oacc[dt][2] * inv, oacc[dt][3] * inv);
-        *reinterpret_cast<uint2*>(tcol + (dt >> 1) * 32 + ((dt & 1) ? todd : 0)) = w;
+        const int at = TILES ? (dt >> 1) * 32 + grp * 8 + (dt & 1) * 4 : dt * 16 + 4 * grp;
+        *reinterpret_cast<uint2*>(tb + col * TBS + at) = w;
       }
       if (valid && grp == 0) part_lse[pidx] = l > 0.f ? m + fast_log2(l) : -INFINITY;
       wave_sync();
@@ -1585,21 +1592,28 @@ static hipError_t launch_block_path(const Shape& s, const Geo& geo, const void* 
       const uint16_t* vv = static_cast<const uint16_t*>(v);
       // Eight wavefronts share the staged block: with blocks of up to 64 keys
       // two workgroups (16 wavefronts) fit a CU, with larger blocks one.
-      auto go = [&](auto kern, int nw) {
+      auto go = [&](auto kern) {
         const size_t lds = (static_cast<size_t>(s.C) * (D + 8) + static_cast<size_t>(D) * (s.C + 4) +
-                            static_cast<size_t>(nw) * 16 * (D + 8)) * 2;
+                            static_cast<size_t>(kAttnBlockWaves) * 16 * (D + 8)) * 2;
         if (lds > 65536) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-        kern<<<grid, nw * 64, lds, st>>>(a, qq, kk, vv, co.offs, co.toffs, co.ncl, co.pairs, part_o, part_lse);
+        kern<<<grid, kAttnBlockWaves * 64, lds, st>>>(a, qq, kk, vv, co.offs, co.toffs, co.ncl, co.pairs, part_o,
+                                                      part_lse);
       };
-      if (s.C == 32)
-        go(attn_block16_kernel<D, 1, kAttnBlockWaves>, kAttnBlockWaves);
-      else if (s.C == 64)
-        go(attn_block16_kernel<D, 2, kAttnBlockWaves>, kAttnBlockWaves);
-      else if (s.C == 96)
-        go(attn_block16_kernel<D, 3, kAttnBlockWaves>, kAttnBlockWaves);
-      else
-        go(attn_block16_kernel<D, 4, kAttnBlockWaves>, kAttnBlockWaves);
+      auto by_order = [&](auto ct) {
+        constexpr int CT = decltype(ct)::value;
+        constexpr bool kMayPair = D == 64 && CT == 4;
+        auto pick = [&](auto paired) {
+          if (a.tile_order) go(attn_block16_kernel<D, CT, kAttnBlockWaves, true, decltype(paired)::value>);
+          else go(attn_block16_kernel<D, CT, kAttnBlockWaves, false, decltype(paired)::value>);
+        };
+        if (kMayPair && s.G <= 2) pick(std::bool_constant<kMayPair>{});
+        else pick(std::false_type{});
+      };
+      if (s.C == 32) by_order(std::integral_constant<int, 1>{});
+      else if (s.C == 64) by_order(std::integral_constant<int, 2>{});
+      else if (s.C == 96) by_order(std::integral_constant<int, 3>{});
+      else by_order(std::integral_constant<int, 4>{});
     }
     // With several heads per KV head, the row tiles of this chunk that the
     // union kernel did not take go through the row-tile kernel of
