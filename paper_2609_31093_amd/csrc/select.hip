@@ -2634,14 +2634,6 @@ __device__ __forceinline__ int walk_levels(const SelArgs& a, int c, int lane, co
   return nA;
 }
 
-// ----------------------------------------------------------------------------
-// Leaf scoring for few rows (decode): one workgroup per (row, candidate slot)
-// computes the exact LSE over the candidate block's raw keys for the G query
-// heads of the KV head (Sec. 3.3 leaf level; the same u as the clustered
-// scorers, in log2 units).  Up to 64 key rows are requested at once, so a
-// step costs a few memory round trips whatever the number of rows; key-block
-// reuse across queries, the reason for clustering, does not arise here.
-// ----------------------------------------------------------------------------
 // The same walk for 64 < g*K <= 128: two candidates per lane, ranked as in
 // select_kernel, the lists in LDS (list: [128], ascending all the way down;
 // flag: [128], next: [128]).  Returns their number.
@@ -2713,6 +2705,14 @@ __device__ __forceinline__ int walk_levels128(const SelArgs& a, int c, int lane,
   return nA;
 }
 
+// ----------------------------------------------------------------------------
+// Leaf scoring for few rows (decode): one workgroup per (row, candidate slot)
+// computes the exact LSE over the candidate block's raw keys for the G query
+// heads of the KV head (Sec. 3.3 leaf level; the same u as the clustered
+// scorers, in log2 units).  Up to 64 key rows are requested at once, so a
+// step costs a few memory round trips whatever the number of rows; key-block
+// reuse across queries, the reason for clustering, does not arise here.
+// ----------------------------------------------------------------------------
 // WALK: the candidates come from the node scores (every workgroup of a row
 // walks for itself; the first one stores the list for the final Top-K).
 template <typename T, int D, int GMAX, bool WALK>
@@ -3248,8 +3248,6 @@ hipError_t launch_select_two_stage(const Shape& s, const Geo& geo, const void* q
   return hipSuccess;
 }
 
-// Split schedule: stage 1 with a workgroup per row, every scored leaf
-// candidate on a workgroup of its own, then the final Top-K.
 // Node scores up front: the ranked levels' nodes (levels 2 .. top with more
 // than K of them) as one list per row, when
 //   * at least two levels are ranked (with one, the walk waits once as well; but
@@ -3260,8 +3258,9 @@ hipError_t launch_select_two_stage(const Shape& s, const Geo& geo, const void* q
 //   * at most kNodeScoreGroups leaf-scoring workgroups walk, 4 per CU (32 rows
 //     of 4 heads, 20011 tokens: 59.0 -> 51.9 us; 64 rows of one head, 16384
 //     tokens, where twice as many walk: 43.6 against 49.1); with g*K > 64,
-//     where the other path is select_kernel, four times that (2 rows, 524288
-//     tokens, 128-key blocks, g = 4, K = 32: 162 -> 53 us a step).
+//     where the other path is select_kernel, four times that (the selection of 2
+//     rows of 4 heads, 524288 tokens, 128-key blocks, g = 4, K = 32: 107 -> 27 us; of
+//     32 rows of one head, 20000 tokens, 32-key blocks: 49 -> 39).
 constexpr int64_t kNodeScoreBytes = 32ll << 20;
 constexpr int kNodeScoreMax = 8192;
 constexpr int64_t kNodeScoreGroups = 1024;
@@ -3308,6 +3307,11 @@ size_t select_split_ws(const Shape& s, const Geo& geo) {
   return split_layout(s).total + align256(static_cast<size_t>(s.BH()) * s.Nq * node_scores(s, geo).stride * 4);
 }
 
+// Split schedule: the intermediate levels, every scored leaf candidate on a
+// workgroup of its own, then the final Top-K.  The levels are walked from node
+// scores computed up front, by the leaf-scoring workgroups themselves, where
+// node_scores() allows it and the workspace holds them; otherwise level by
+// level on a workgroup per row.
 hipError_t launch_select_split(const Shape& s, const Geo& geo, const void* q, const void* k, const float* pyr,
                                int32_t* idx, float* score, void* ws, size_t ws_bytes, hipStream_t st) {
   const SplitWs w = split_layout(s);
