@@ -178,34 +178,44 @@ constexpr int64_t kSplitMaxRows = 2048;
 
 // Fewer rows than kTwoStageRows: does grouping the leaf pairs by key block
 // pay?  Only rows of one (batch, KV head) share its key blocks, and the
-// grouping costs 30 us and more, the longer the more rows a head has (few
+// grouping costs 30 us and more, the longer the more pairs a head has (few
 // workgroups count and place them), against leaf scores that the split
 // schedule (up to 2048 rows) or the fused one spreads over the device.
-//   * A row scores the min(g*K, M1) candidates of the leaf level when there are
-//     more than K of them: M1 >= 2 K (g*K = 128 over 32 blocks, 2 x 1500 rows of 4
-//     heads: 17 us fused, 199 grouped).
-//   * Four rows to a key block, or one per 16 keys where that is more: decode,
-//     however many sequences, is not grouped (512 KV heads x 1 row of 4 heads,
-//     131072 keys: 127 us split, 1508 grouped; 16 KV heads x 64 rows, 32768
-//     keys, 4 rows to a block: 155 and 122; 32 x 32 rows, 2 to a block: 159
-//     and 170).
-//   * Work to save: keys x dims x heads of one row's scored candidates, over
-//     the KV heads.  Up to four heads, g*K = 32, 64-key blocks, d = 128, over
-//     8192 keys: 2 KV heads x 1024 rows of 4 heads 259 and 223 us, 8 x 256 rows
-//     260 and 100; 4 x 512 rows of one head 129 and 97, 2 x 1024 rows 128 and
-//     150.  d = 64, g*K = 16, 4000 rows of one head on one KV head: 33 and 100.
-//   * More than four heads, where the other schedules have no kernel that
-//     shares loads among them: above the split schedule's range (16 heads,
-//     2 x 1025 rows, g*K = 16, 30000 keys: 1158 and 529); not for lists of a
-//     few candidates (g*K = 8: 570 and 650).
-// Over 7298 shapes (1 to 300 KV heads, 8 to 256 candidates, 32- to 256-key
-// blocks) the choice is more than 4% slower than the other one at 5.
+//   * pairs, those of one head, against its key blocks.  One row to a
+//     block is enough where several heads of the row want it too, two for a
+//     single head; half a row above the split schedule's range.  Decode, however
+//     many sequences, has no two (512 KV heads x 1 row of 4 heads, 131072 keys:
+//     127 us split, 1508 grouped; 16 x 64 rows, 32768 keys: 155 and 122).
+//   * work = keys x dims x heads of one row's scored candidates, over the KV
+//     heads: many short lists are spread widely either way (d = 64, g*K = 16,
+//     4000 rows of one head on one KV head: 33 us fused, 100 grouped), long or
+//     wide ones are not (2048 rows of 4 heads on one KV head, g*K = 128,
+//     128-key blocks over 131072 keys: 1562 split, 527 grouped).  Up to 1024
+//     rows of one KV head are counted by so few workgroups that it takes four
+//     times the work (4 heads, g*K = 32, 8192 keys, 1024 rows: 131 and 203;
+//     2048: 247 and 218).
+//   * Lists of at most 16 candidates (8 with more than four heads) have fused
+//     kernels of their own and want more of both (g*K = 8, d = 128, 2 x 1050
+//     rows of 4 heads: 45 fused, 129 grouped; 128 x 17 of 16: 423 and 81).
+//   * More than four heads, where no other kernel shares loads among them: above
+//     the split schedule's range already where a third of a head per block is
+//     shared (16 heads, g*K = 16, 2100 KV heads x 1 row over 33, 129 and 513
+//     blocks: 1096, 1226 and 1370 fused, 537, 876 and 1959 grouped).
+// Over 7298 shapes of 512 to 4095 rows (1 to 300 KV heads, 8 to 256 candidates,
+// 32- to 256-key blocks) the mean time is 1.0% above that of the faster
+// schedule for each; grouping them all is 6.2% above it.
 bool two_stage_pays(const pisa::Shape& s, const pisa::Geo& g, int64_t rows) {
   const int64_t M1 = g.M[1], scored = std::min<int64_t>(s.gK(), M1) - s.K;
-  if (M1 < 2 * s.K || 16LL * s.Nq * s.gK() < std::max(64, s.C) * M1) return false;
-  if (s.G > 4) return rows > kSplitMaxRows && scored >= 8;
-  if (rows * s.G < kSplitMaxRows || scored < 16 || (s.BH() < 2 && rows <= kSplitMaxRows)) return false;
-  return static_cast<int64_t>(s.BH()) * s.G * s.C * s.D * scored >= 1 << 20;
+  if (scored <= 0) return false;
+  const int64_t pairs = s.Nq * scored, work = static_cast<int64_t>(s.BH()) * s.G * s.C * s.D * scored;
+  if (rows <= kSplitMaxRows) {
+    if (s.G > 4 || rows * s.G < kSplitMaxRows) return false;
+    const int64_t least = (s.G <= 2 ? 224 << 10 : 384 << 10) * (s.BH() == 1 && rows <= 1024 ? 4 : 1);
+    return pairs >= (s.G == 1 ? 2 : 1) * M1 && work >= least;
+  }
+  if (s.gK() <= (s.G <= 4 ? 16 : 8)) return pairs >= 2 * M1 && work >= (s.G <= 4 ? 2 << 20 : 4 << 20);
+  if (s.G > 4) return 3 * s.G * pairs >= M1;
+  return 2 * pairs >= M1 && work >= 64 << 10;
 }
 
 // From this many rows the automatic schedule insists on the two-stage
