@@ -64,17 +64,18 @@ def test_small_workspace_is_smaller():
 
 
 @pytest.mark.parametrize("shape", [
-    # (B, H, Hkv, Nq, N, d, C, g, K, causal): the automatic schedule's range between split and 4096 rows
-    (1, 4, 1, 512, 9001, 128, 64, 2, 16, 1),     # from 512 rows with four heads
-    (1, 1, 1, 2047, 6000, 64, 64, 2, 8, 1),      # one below, and at, the 2048 rows of single heads
+    # (B, H, Hkv, Nq, N, d, C, g, K, causal): rows where the automatic schedule may group
+    (1, 4, 1, 512, 9001, 128, 64, 2, 16, 1),     # split: few rows of one KV head
+    (1, 1, 1, 2047, 6000, 64, 64, 2, 8, 1),      # split, one below and at the line of single heads: little work
     (1, 1, 1, 2048, 6000, 64, 64, 2, 8, 1),
-    (1, 16, 1, 2049, 6000, 64, 64, 2, 8, 1),     # sixteen heads, above the split range
-    (1, 4, 2, 1100, 20000, 128, 128, 4, 32, 0),  # 128 candidates
-    (3, 3, 1, 800, 3000, 64, 32, 3, 7, 1),
+    (1, 16, 1, 2049, 6000, 64, 64, 2, 8, 1),     # grouped: sixteen heads, above the split range
+    (1, 4, 2, 1100, 20000, 128, 128, 4, 32, 0),  # grouped, 128 candidates
+    (3, 3, 1, 800, 3000, 64, 32, 3, 7, 1),       # grouped, three heads
 ])
 def test_middle_rows(shape):
-    """With the full workspace the leaf pairs are grouped by key block; without
-    any, as callers of these sizes could have had, the other schedules run."""
+    """The schedule that the full workspace gets, grouped by key block where that
+    pays, and the one of callers with the least workspace (none, or the split
+    schedule's smallest)."""
     B, H, Hkv, Nq, N, d, C, g, K, causal = shape
     x = inputs.random_qkv(B, H, Hkv, Nq, N, d, "bf16", seed=52)
     p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, g, K, causal, "bf16")
