@@ -129,8 +129,8 @@ __global__ __launch_bounds__(64) void bsa_rows_kernel(BsaArgs a) {
       }
     }
     if (lane == 0) {
-      outl[r] = bi;
-      sc[bi] = -INFINITY;
+      outl[r] = bi;  // 0x7fffffff: nothing left that can be ranked (NaN, -inf)
+      if (bi < E) sc[bi] = -INFINITY;
     }
     wave_sync();
   }
@@ -147,8 +147,8 @@ __global__ __launch_bounds__(64) void bsa_rows_kernel(BsaArgs a) {
   for (int j = lane; j < a.K; j += 64) {
     const int v = outl[j];
     int rank = 0;
-    for (int i = 0; i < a.K; ++i) rank += outl[i] < v ? 1 : 0;
-    out[rank] = v;
+    for (int i = 0; i < a.K; ++i) rank += outl[i] < v || (outl[i] == v && i < j) ? 1 : 0;
+    out[rank] = v < E ? v : -1;
   }
 }
 

@@ -138,3 +138,27 @@ def test_blocks_of_minus_infinity_rank_last(dtype, H, Hkv):
     is_forced = (kept[..., None] == forced[None, None, :, None]).any(-1)
     took_bad = (torch.isneginf(ref) & (idx >= 0) & ~is_forced).any(-1)
     assert bool(left_finite.any()) and not bool((left_finite & took_bad).any())
+
+
+@pytest.mark.parametrize("dtype,H,K", [("f32", 1, 7), ("f32", 4, 5), ("f32", 5, 40), ("bf16", 1, 40)])
+@pytest.mark.parametrize("what", ["nan", "-inf"])
+def test_flat_rows_with_nothing_left_to_rank(dtype, H, K, what):
+    """The flat baseline row by row, with fewer blocks that can be ranked than
+    are kept: the forced ones and those, ascending, then -1."""
+    B, Hkv, Nq, N, d, C = 1, 1, 70, 3000, 64, 32
+    x = inputs.random_qkv(B, H, Hkv, Nq, N, d, dtype, seed=64)
+    p = pisa.make_problem(B, H, Hkv, Nq, N, d, C, 2, K, 1, dtype)
+    q, k = dev(x["q"], dtype), dev(x["k"], dtype)
+    if what == "nan":
+        k[:, :, 3 * C:] = float("nan")
+    else:
+        q[..., 0] = 1.0
+        k[:, :, 3 * C:, 0] = float("-inf")
+    idx = pisa.select_flat_bsa(p, q, pisa.build_pyramid(p, k)).cpu().numpy()[0, 0]
+    for r in range(Nq):
+        c = (N - Nq + r) // C
+        got = idx[r][idx[r] >= 0]
+        assert np.all(np.diff(got) > 0) and np.all(idx[r][len(got):] == -1)
+        assert {0, c - 1, c} <= set(got) <= {0, 1, 2, c - 1, c}
+        if H == 1:
+            assert len(got) == 5
