@@ -237,6 +237,10 @@ __global__ __launch_bounds__(256) void quality_rank_kernel(QualityArgs a, const 
         }
       }
       wg_argmax(v, bi, sv, si);
+      if (bi >= nE) {  // nothing left that can be ranked (NaN masses)
+        nref = n;
+        break;
+      }
       if (tid == 0) {
         taken[bi] = 1;
         kept[n] = bi;

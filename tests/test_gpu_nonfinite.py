@@ -162,3 +162,22 @@ def test_flat_rows_with_nothing_left_to_rank(dtype, H, K, what):
         assert {0, c - 1, c} <= set(got) <= {0, 1, 2, c - 1, c}
         if H == 1:
             assert len(got) == 5
+
+
+def test_quality_of_masses_that_cannot_be_ranked():
+    """Rows of NaN queries have NaN masses: their reference is the forced
+    blocks; the other rows' is what it is without the NaN."""
+    B, H, Hkv, N, d, C, K = 1, 2, 1, 2000, 64, 32, 6
+    x = inputs.random_qkv(B, H, Hkv, N, N, d, "bf16", seed=65)
+    p = pisa.make_problem(B, H, Hkv, N, N, d, C, 2, K, 1, "bf16")
+    q, k = dev(x["q"], "bf16"), dev(x["k"], "bf16")
+    idx = pisa.select(p, q, k, pisa.build_pyramid(p, k))
+    rows = torch.tensor([0, 500, 959, 960, 1500, 1999], dtype=torch.int32, device="cuda")
+    met, want = pisa.selection_quality(p, q, k, idx, rows)
+    q[:, :, 960:] = float("nan")
+    met2, ref = pisa.selection_quality(p, q, k, idx, rows)
+    torch.cuda.synchronize()
+    assert torch.equal(ref[0, 0, :3], want[0, 0, :3]) and torch.equal(met2[0, 0, :3], met[0, 0, :3])
+    for i in range(3, 6):
+        c = int(rows[i]) // C
+        assert ref[0, 0, i].tolist() == [0, c - 1, c] + [-1] * (K - 3)
